@@ -69,7 +69,7 @@ def sched_name(s):
     return base + ("+persistent" if s & 0x10 else "") + ("+xcd-local" if s & 0x20 else "")
 
 # sources of the interaction kernels (the counter record names their hash)
-INTERACTION_SOURCES = ("ot_common.h", "ot_interact.h")
+INTERACTION_SOURCES = ("ot_common.h", "ot_interact.h", "ot_pair.h")
 
 
 def log(*a):

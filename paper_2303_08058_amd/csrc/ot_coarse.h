@@ -4,8 +4,8 @@
 // neighbour in slot s is missing and is covered by octant o of a
 // parent-level node P, each of the 4^3 coarse cells J of that octant stands
 // in for its 2x2x2 fine children when all of them would be in the target
-// cell's stencil. Included by ot_fmm.hip after ot_interact.h (uses its
-// derivatives, trace-reduced contraction and staging scales).
+// cell's stencil. Included by ot_fmm.hip after ot_interact.h (uses the
+// pair arithmetic of ot_pair.h).
 #pragma once
 
 #include "ot_interact.h"
@@ -52,17 +52,17 @@ struct CoarseShape {
 // With 8 wavefronts (a whole target) the accumulators go through LDS at the
 // end so that L is read and written in cell order; smaller work-groups add
 // into their cells directly. FULL: the full truncation (every |b| <= 3 for
-// every |a| <= 3, derivatives of G to order 6), with the same staged values
-// and kept outputs as the total order; its derivatives need up to 256
-// registers, so it runs at half the waves per SIMD.
+// every |a| <= 3), with the same kept outputs as the total order; its pair step
+// needs about 150 registers, so it runs at half the waves per SIMD.
 template <int NW, bool FULL>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(FULL ? 2 : 4)))
 k_coarse_fine(const CoarseParams p)
 {
     using Sh = CoarseShape<NW>;
-    constexpr int kNc = 3 + kNRed;                        // staged values per coarse cell
-    constexpr int kNa = ModeTraits<MODE_FWD_STORE>::nacc;  // kept L_a of the reduced form (either truncation)
-    static_assert(ModeTraits<MODE_FULL_STORE>::nacc == kNa, "both truncations keep the same outputs");
+    constexpr int kSums = FULL ? SUMS_X3 : SUMS_F3;
+    constexpr int kNc = record_size(kSums) - 1;  // staged values per coarse cell: the record less Q_zz
+    constexpr int kZz = 12;                      // Q_zz = -(Q_xx + Q_yy)
+    constexpr int kNa = sums_count(kSums);
     constexpr int kSlotVals = kNc * 64;
     __shared__ double s_src[Sh::batch * kSlotVals];
     __shared__ int s_slot[Sh::batch];
@@ -96,30 +96,23 @@ k_coarse_fine(const CoarseParams p)
                 s_shift[tid][k] = (double)(int)(int8_t)((packed >> (8 * k)) & 0xff) * p.period[k];
         }
         __syncthreads();
-        // a thread's values four at a time (their loads in flight together;
-        // no load depends on another)
-        constexpr int kIter = (Sh::batch * kSlotVals + NW * 64 - 1) / (NW * 64);
-#pragma unroll 4
-        for (int i = 0; i < kIter; ++i) {
-            const int v = tid + i * NW * 64;
-            if (v < nb * kSlotVals) {
-                const int b = v / kSlotVals, r = v - b * kSlotVals;
-                const int k = r >> 6, J = r & 63;
-                const int4 e = s_ent[b];
-                const int o = e.z;
-                const int cx = J & 3, cy = (J >> 2) & 3, cz = J >> 4;
-                const int pc = (cx + 4 * (o & 1)) + 8 * (cy + 4 * ((o >> 1) & 1)) + 64 * (cz + 4 * (o >> 2));
-                const long jj = (long)e.y * kSub3 + pc;
-                double val;
-                if (k < 3) {
-                    val = p.pos_c[k * p.c_stride + jj] + s_shift[b][k];
-                } else {
-                    const int cP = c_red_src[k - 3][0], cS = c_red_src[k - 3][1];
-                    val = c_scale_fwd[cP] * p.mom_c[cP * p.c_stride + jj];
-                    if (cS >= 0) val -= c_scale_fwd[cS] * p.mom_c[cS * p.c_stride + jj];
-                }
-                s_src[v] = val;
-            }
+        // one coarse cell per thread, its 23 loads in flight together
+        static_assert(Sh::batch * 64 == NW * 64, "a thread per staged coarse cell");
+        const int sb = tid >> 6, sJ = tid & 63;
+        if (sb < nb) {
+            const int4 e = s_ent[sb];
+            const int o = e.z;
+            const int cx = sJ & 3, cy = (sJ >> 2) & 3, cz = sJ >> 4;
+            const int pc = (cx + 4 * (o & 1)) + 8 * (cy + 4 * ((o >> 1) & 1)) + 64 * (cz + 4 * (o >> 2));
+            const long jj = (long)e.y * kSub3 + pc;
+            double raw[20], rec[20];
+#pragma unroll
+            for (int c = 0; c < 20; ++c) raw[c] = p.mom_c[c * p.c_stride + jj];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) rec[k] = p.pos_c[k * p.c_stride + jj] + s_shift[sb][k];
+            stage_record<kSums, false>(raw, rec);
+#pragma unroll
+            for (int k = 0; k < kNc; ++k) s_src[sb * kSlotVals + k * 64 + sJ] = rec[k < kZz ? k : k + 1];
         }
         __syncthreads();
         // one loop over the lane's (slot, coarse cell) pairs of the batch, so
@@ -138,21 +131,14 @@ k_coarse_fine(const CoarseParams p)
             const int J = __builtin_ctzll(cur);
             cur &= cur - 1;
             const double* src = s_src + b * kSlotVals + J;
-            double f[kNc];
+            double f[kNc + 1];
 #pragma unroll
-            for (int k = 0; k < kNc; ++k) f[k] = src[k * 64];
-            if constexpr (FULL) {
-                double D[7];
-                const double rr[3] = {xi - f[0], yi - f[1], zi - f[2]};
-                radial<6>(rr[0], rr[1], rr[2], D);
-                contract_full<0>(acc, f + 3, rr, D, std::make_integer_sequence<int, 20>{});
-            } else {
-                double G[20];
-                green<3>(xi - f[0], yi - f[1], zi - f[2], G);
-                contract_red<0, TRUNC3>(acc, f + 3, G, std::make_integer_sequence<int, 20>{});
-            }
+            for (int k = 0; k < kNc; ++k) f[k < kZz ? k : k + 1] = src[k * 64];
+            f[kZz] = -(f[7] + f[10]);
+            pair_sums<kSums>(acc, f, xi - f[0], yi - f[1], zi - f[2]);
         }
     }
+    finish_sums<kSums>(acc);
     int oc = cell;
     if constexpr (NW == 8) {
         // back to cell order through LDS

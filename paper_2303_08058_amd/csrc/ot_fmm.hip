@@ -24,11 +24,10 @@
 //    VALU add per offset for the LDS address. Bank mapping of the 8x8 lane
 //    pattern with 24-wide rows is conflict-free for ds_read_b64.
 //  * All arithmetic is FP64 VALU: per pair one rsqrt (v_rsq_f64 plus a
-//    third-order Newton correction), the derivatives of 1/r from the radial
-//    factors D_n = (-1)^{n+1} (2n-1)!! / r^{2n+1}, and the contraction
-//    (84 FMAs for the multipole). Source moments are pre-scaled by s_beta
-//    when staged, so the inner loop is FMAs only. There is no shared dense
-//    operand between pairs, so MFMA does not apply.
+//    third-order Newton correction), the radial factors D_n = (-1)^{n+1}
+//    (2n-1)!! / r^{2n+1}, and the contraction arranged around the separation
+//    vector (ot_pair.h). Sources are scaled and made trace-free when staged.
+//    There is no shared dense operand between pairs, so MFMA does not apply.
 //  * Missing neighbours are staged as zero moments at a far, finite centre:
 //    their terms are exact zeros, identical to dropping the pairs.
 //  * The adjoint is two gather passes with the same skeleton (no atomics):

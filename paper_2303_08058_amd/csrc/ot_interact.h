@@ -20,29 +20,11 @@
 
 #include "ot_common.h"
 #include "ot_fmm.h"
+#include "ot_pair.h"
 
 using namespace otfmm;
 
 namespace {
-
-// Staging scale of the source components: forward sources carry
-// s_beta = (-1)^{|beta|}/beta!, adjoint sources carry (-1)^{|alpha|}.
-__constant__ double c_scale_fwd[20] = {
-    parity_sign(0) * inv_multi_factorial(0),   parity_sign(1) * inv_multi_factorial(1),
-    parity_sign(2) * inv_multi_factorial(2),   parity_sign(3) * inv_multi_factorial(3),
-    parity_sign(4) * inv_multi_factorial(4),   parity_sign(5) * inv_multi_factorial(5),
-    parity_sign(6) * inv_multi_factorial(6),   parity_sign(7) * inv_multi_factorial(7),
-    parity_sign(8) * inv_multi_factorial(8),   parity_sign(9) * inv_multi_factorial(9),
-    parity_sign(10) * inv_multi_factorial(10), parity_sign(11) * inv_multi_factorial(11),
-    parity_sign(12) * inv_multi_factorial(12), parity_sign(13) * inv_multi_factorial(13),
-    parity_sign(14) * inv_multi_factorial(14), parity_sign(15) * inv_multi_factorial(15),
-    parity_sign(16) * inv_multi_factorial(16), parity_sign(17) * inv_multi_factorial(17),
-    parity_sign(18) * inv_multi_factorial(18), parity_sign(19) * inv_multi_factorial(19)};
-__constant__ double c_scale_rev[20] = {
-    parity_sign(0),  parity_sign(1),  parity_sign(2),  parity_sign(3),  parity_sign(4),
-    parity_sign(5),  parity_sign(6),  parity_sign(7),  parity_sign(8),  parity_sign(9),
-    parity_sign(10), parity_sign(11), parity_sign(12), parity_sign(13), parity_sign(14),
-    parity_sign(15), parity_sign(16), parity_sign(17), parity_sign(18), parity_sign(19)};
 
 // ---------------------------------------------------------------------------
 // Stencil: for target parity (0, 0, pz), the offsets d = j - i grouped into
@@ -179,102 +161,11 @@ const SlotCounts& slot_counts()
 }
 
 // ---------------------------------------------------------------------------
-// Per-pair arithmetic
+// Kept outputs: within a group of outputs of one order and one truncation,
+// every output whose z exponent is 2 or more follows from two others,
+// L_{g+zz} = -(L_{g+xx} + L_{g+yy}) (the derivatives of 1/r are trace-free),
+// and is rebuilt after the sum.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double rsqrt_fp64(double a)
-{
-    // hardware estimate, then y (1 + e/2 + 3e^2/8) with e = 1 - a y^2
-    double y = __builtin_amdgcn_rsq(a);
-    const double e = __builtin_fma(-a * y, y, 1.0);
-    y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
-    return y;
-}
-
-// G_gamma(r), |gamma| <= ORD (3 or 4), graded-lex order, from the radial
-// factors D0 = -1/r, D1 = 1/r^3, D2 = -3/r^5, D3 = 15/r^7, D4 = -105/r^9:
-//   G_a = r_a D1, G_ab = r_a r_b D2 + d_ab D1,
-//   G_abc = r_a r_b r_c D3 + (d_ab r_c + d_ac r_b + d_bc r_a) D2,
-//   G_abcd = r_a r_b r_c r_d D4 + (sum of 6 d r r) D3 + (sum of 3 d d) D2.
-template <int ORD>
-__device__ __forceinline__ void green(double x, double y, double z, double* G)
-{
-    const double r2 = __builtin_fma(x, x, __builtin_fma(y, y, z * z));
-    const double ri = rsqrt_fp64(r2);
-    const double ri2 = ri * ri;
-    const double D1 = ri * ri2;
-    const double D2 = -3.0 * D1 * ri2;
-    const double D3 = -5.0 * D2 * ri2;
-    G[0] = -ri;
-    G[1] = x * D1;
-    G[2] = y * D1;
-    G[3] = z * D1;
-    const double xD2 = x * D2, yD2 = y * D2, zD2 = z * D2;
-    G[4] = __builtin_fma(x, xD2, D1);
-    G[5] = x * yD2;
-    G[6] = x * zD2;
-    G[7] = __builtin_fma(y, yD2, D1);
-    G[8] = y * zD2;
-    const double xD3 = x * D3, yD3 = y * D3, zD3 = z * D3;
-    const double xx3 = x * xD3, xy3 = x * yD3, xz3 = x * zD3;
-    const double yy3 = y * yD3, yz3 = y * zD3;
-    G[10] = __builtin_fma(x, xx3, 3.0 * xD2);  // xxx
-    G[11] = __builtin_fma(y, xx3, yD2);        // xxy
-    G[12] = __builtin_fma(z, xx3, zD2);        // xxz
-    G[13] = __builtin_fma(x, yy3, xD2);        // xyy
-    G[14] = z * xy3;                           // xyz
-    G[16] = __builtin_fma(y, yy3, 3.0 * yD2);  // yyy
-    G[17] = __builtin_fma(z, yy3, zD2);        // yyz
-    // components with z^2 from the trace (Laplace: G_{g+xx} + G_{g+yy} + G_{g+zz} = 0)
-    G[9] = -(G[4] + G[7]);     // zz
-    G[15] = -(G[10] + G[13]);  // xzz
-    G[18] = -(G[11] + G[16]);  // yzz
-    G[19] = -(G[12] + G[17]);  // zzz
-    if constexpr (ORD >= 4) {
-        const double D4 = -7.0 * D3 * ri2;
-        const double xD4 = x * D4, yD4 = y * D4;
-        const double xx4 = x * xD4, yy4 = y * yD4;
-        G[20] = __builtin_fma(x * x, xx4, __builtin_fma(6.0, xx3, 3.0 * D2));  // xxxx
-        G[21] = __builtin_fma(x * y, xx4, 3.0 * xy3);                         // xxxy
-        G[22] = __builtin_fma(x * z, xx4, 3.0 * xz3);                         // xxxz
-        G[23] = __builtin_fma(y * y, xx4, __builtin_fma(1.0, xx3 + yy3, D2)); // xxyy
-        G[24] = __builtin_fma(y * z, xx4, yz3);                               // xxyz
-        G[26] = __builtin_fma(x * y, yy4, 3.0 * xy3);                         // xyyy
-        G[27] = __builtin_fma(x * z, yy4, xz3);                               // xyyz
-        G[30] = __builtin_fma(y * y, yy4, __builtin_fma(6.0, yy3, 3.0 * D2)); // yyyy
-        G[31] = __builtin_fma(y * z, yy4, 3.0 * yz3);                         // yyyz
-        G[25] = -(G[20] + G[23]);  // xxzz
-        G[28] = -(G[21] + G[26]);  // xyzz
-        G[29] = -(G[22] + G[27]);  // xzzz
-        G[32] = -(G[23] + G[30]);  // yyzz
-        G[33] = -(G[24] + G[31]);  // yzzz
-        G[34] = -(G[25] + G[32]);  // zzzz
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Trace-reduced contractions. Every derivative of 1/r of order >= 2 is
-// trace-free (Laplace's equation): G_{g+xx} + G_{g+yy} + G_{g+zz} = 0. So
-//  * source side: a complete order-2 or order-3 shell of source components
-//    contracts through 16 combinations instead of 20 -- q_xx - q_zz and
-//    q_yy - q_zz (paired with G_{.+xx}, G_{.+yy}); q_xxx - q_xzz,
-//    q_xyy - q_xzz, q_xxy - q_yzz, q_yyy - q_yzz, q_xxz - q_zzz,
-//    q_yyz - q_zzz and q_xyz for order 3;
-//  * output side: within a group of outputs of one order and one truncation,
-//    every output whose z exponent is >= 2 follows from two others,
-//    L_{g+zz} = -(L_{g+xx} + L_{g+yy}), and is rebuilt after the sum.
-// The results equal the plain contraction up to rounding.
-// ---------------------------------------------------------------------------
-constexpr int kNRed = 16;
-// reduced component b = q[kRedP[b]] - q[kRedS[b]] (kRedS = -1: q[kRedP[b]]);
-// it pairs with G_{g + kRedP[b]}
-constexpr int kRedP[kNRed] = {0, 1, 2, 3, 4, 7, 5, 6, 8, 10, 13, 11, 16, 12, 17, 14};
-constexpr int kRedS[kNRed] = {-1, -1, -1, -1, 9, 9, -1, -1, -1, 15, 15, 18, 18, 19, 19, -1};
-__constant__ int c_red_src[kNRed][2] = {
-    {kRedP[0], kRedS[0]},   {kRedP[1], kRedS[1]},   {kRedP[2], kRedS[2]},   {kRedP[3], kRedS[3]},
-    {kRedP[4], kRedS[4]},   {kRedP[5], kRedS[5]},   {kRedP[6], kRedS[6]},   {kRedP[7], kRedS[7]},
-    {kRedP[8], kRedS[8]},   {kRedP[9], kRedS[9]},   {kRedP[10], kRedS[10]}, {kRedP[11], kRedS[11]},
-    {kRedP[12], kRedS[12]}, {kRedP[13], kRedS[13]}, {kRedP[14], kRedS[14]}, {kRedP[15], kRedS[15]}};
-
 __host__ __device__ constexpr bool kept(int g) { return exp_of(g).c < 2; }
 
 // position of a kept multi-index among the kept ones of [lo, g)
@@ -285,50 +176,7 @@ __host__ __device__ constexpr int kept_slot(int lo, int g)
     return n;
 }
 
-constexpr bool check_reduction()
-{
-    for (int b = 0; b < kNRed; ++b) {
-        if (kRedS[b] < 0) continue;
-        // the eliminated component is the primary one with an xx (or yy) traded for zz
-        const Exp3 p = exp_of(kRedP[b]), q = exp_of(kRedS[b]);
-        const bool via_x = p.a >= 2 && q.a == p.a - 2 && q.b == p.b && q.c == p.c + 2;
-        const bool via_y = p.b >= 2 && q.b == p.b - 2 && q.a == p.a && q.c == p.c + 2;
-        if (!via_x && !via_y) return false;
-    }
-    return kept_slot(0, 20) == 16 && kept_slot(1, 35) == 24;
-}
-static_assert(check_reduction(), "trace reduction tables");
-
-// truncation rules: acc over outputs g (range [LO, LO + N)) and reduced sources b
-enum Trunc : int { TRUNC3 = 0, TRUNC4 = 1, EXACT4 = 2 };
-
-__host__ __device__ constexpr bool allowed(int rule, int og, int ob)
-{
-    return rule == TRUNC3 ? og + ob <= 3 : (rule == TRUNC4 ? og + ob <= 4 : og + ob == 4);
-}
-
-template <int LO, int RULE, int G_, int B>
-__device__ __forceinline__ void term_red(double* acc, const double* r, const double* G)
-{
-    if constexpr (kept(G_) && allowed(RULE, ord_of(G_), ord_of(kRedP[B]))) {
-        constexpr int slot = kept_slot(LO, G_);
-        constexpr int S = sum_idx(G_, kRedP[B]);
-        acc[slot] = __builtin_fma(r[B], G[S], acc[slot]);
-    }
-}
-template <int LO, int RULE, int G_, int... B>
-__device__ __forceinline__ void row_red(double* acc, const double* r, const double* G,
-                                        std::integer_sequence<int, B...>)
-{
-    (term_red<LO, RULE, G_, B>(acc, r, G), ...);
-}
-// acc[kept slot of g] += sum_b r[b] G[g + kRedP[b]] for g in [LO, LO + sizeof...(I))
-template <int LO, int RULE, int... I>
-__device__ __forceinline__ void contract_red(double* acc, const double* r, const double* G,
-                                             std::integer_sequence<int, I...>)
-{
-    (row_red<LO, RULE, LO + I>(acc, r, G, std::make_integer_sequence<int, kNRed>{}), ...);
-}
+static_assert(kept_slot(0, 20) == 16 && kept_slot(1, 35) == 24, "kept outputs");
 
 // full[g - LO] for g in [LO, LO + sizeof...(I)) from the kept accumulators;
 // outputs with z exponent >= 2 are rebuilt in index order (their two
@@ -350,76 +198,6 @@ template <int LO, int... I>
 __device__ __forceinline__ void expand(const double* acc, double* full, std::integer_sequence<int, I...>)
 {
     (expand_one<LO, LO + I>(acc, full), ...);
-}
-
-// ---------------------------------------------------------------------------
-// Full truncation: every output |a| <= 3 keeps every source moment |b| <= 3,
-// so derivatives of G are needed up to order 6. With the radial factors D_p
-// (D_0 = G = -1/r, D_{p+1} = -(2p+1) D_p / r^2, i.e. D_p = d^p G / d(r^2/2)^p)
-// and Phi^(p)_g = d^g D_p, the chain rule d_k D_p = r_k D_{p+1} gives
-//   Phi^(p)_{g+e_k} = r_k Phi^(p+1)_g + g_k Phi^(p+1)_{g-e_k},   G_g = Phi^(0)_g
-// (the same factors give the order <= 4 forms above). The recursion is
-// unrolled at compile time, reducing z first, then x, then y; the compiler
-// merges the repeated subexpressions, so each needed Phi is evaluated once.
-// The trace reduction of sources and outputs holds unchanged: every output
-// keeps complete source shells of orders 2 and 3, and the three outputs
-// L_{g+xx}, L_{g+yy}, L_{g+zz} keep the same sources.
-// ---------------------------------------------------------------------------
-template <int N>
-__device__ __forceinline__ void radial(double x, double y, double z, double* D)
-{
-    const double r2 = __builtin_fma(x, x, __builtin_fma(y, y, z * z));
-    const double ri = rsqrt_fp64(r2);
-    const double ri2 = ri * ri;
-    D[0] = -ri;
-    D[1] = ri * ri2;
-#pragma unroll
-    for (int p = 1; p < N; ++p) D[p + 1] = (-(2.0 * p + 1.0)) * D[p] * ri2;
-}
-
-template <int P, int A, int B, int C>
-__device__ __forceinline__ double phi(const double* r, const double* D)
-{
-    if constexpr (A + B + C == 0) {
-        return D[P];
-    } else if constexpr (C > 0) {
-        const double t = r[2] * phi<P + 1, A, B, C - 1>(r, D);
-        if constexpr (C >= 2) return __builtin_fma((double)(C - 1), phi<P + 1, A, B, C - 2>(r, D), t);
-        else return t;
-    } else if constexpr (A > 0) {
-        const double t = r[0] * phi<P + 1, A - 1, B, C>(r, D);
-        if constexpr (A >= 2) return __builtin_fma((double)(A - 1), phi<P + 1, A - 2, B, C>(r, D), t);
-        else return t;
-    } else {
-        const double t = r[1] * phi<P + 1, A, B - 1, C>(r, D);
-        if constexpr (B >= 2) return __builtin_fma((double)(B - 1), phi<P + 1, A, B - 2, C>(r, D), t);
-        else return t;
-    }
-}
-
-// acc[kept slot of g in [LO, ...)] += sum_b q[b] G_{g + kRedP[b]} over all 16
-// reduced sources
-template <int LO, int G_, int B>
-__device__ __forceinline__ void term_full(double* acc, const double* q, const double* r, const double* D)
-{
-    if constexpr (kept(G_)) {
-        constexpr int slot = kept_slot(LO, G_);
-        constexpr Exp3 e = exp_of(G_);
-        constexpr Exp3 f = exp_of(kRedP[B]);
-        acc[slot] = __builtin_fma(q[B], phi<0, e.a + f.a, e.b + f.b, e.c + f.c>(r, D), acc[slot]);
-    }
-}
-template <int LO, int G_, int... B>
-__device__ __forceinline__ void row_full(double* acc, const double* q, const double* r, const double* D,
-                                         std::integer_sequence<int, B...>)
-{
-    (term_full<LO, G_, B>(acc, q, r, D), ...);
-}
-template <int LO, int... I>
-__device__ __forceinline__ void contract_full(double* acc, const double* q, const double* r, const double* D,
-                                              std::integer_sequence<int, I...>)
-{
-    (row_full<LO, LO + I>(acc, q, r, D, std::make_integer_sequence<int, kNRed>{}), ...);
 }
 
 // Adjoint epilogue: with C_g (g = 1..34, stored at C[g - 1]) the derivative
@@ -518,9 +296,6 @@ struct KParams {
 template <int MODE>
 struct ModeTraits {
     static constexpr bool halo = (MODE == MODE_MONO_HALO || MODE == MODE_FWD_HALO);
-    // staged source components: the mass, or the 16 trace-reduced moments
-    static constexpr int nq = (MODE == MODE_MONO_HALO) ? 1 : kNRed;
-    static constexpr int nc = nq + 3;  // + centre of mass
     static constexpr bool adjoint = (MODE == MODE_B1_STORE || MODE == MODE_B2_STORE || MODE == MODE_B1F_STORE ||
                                      MODE == MODE_B2F_STORE || MODE == MODE_B2S_STORE || MODE == MODE_B2SF_STORE);
     static constexpr bool source_role = (MODE == MODE_B2_STORE || MODE == MODE_B2F_STORE ||
@@ -532,20 +307,21 @@ struct ModeTraits {
     // the F + E sums (total order 3, and the order-4 terms of orders 1..4)
     static constexpr bool fe = (MODE == MODE_B2_STORE || MODE == MODE_B2S_STORE || MODE == MODE_FS_STORE ||
                                 MODE == MODE_AMC_STORE);
-    // accumulators: monopole 20; forward 16 kept of 20; target-role adjoint
-    // 24 kept of the 34 orders 1..4; source-role adjoint and the forward
-    // with saved sums 16 + 24; with the full truncation the source role keeps
-    // one set for orders 0..4 (25)
-    static constexpr int nacc = (MODE == MODE_MONO_HALO)                             ? 20
-                                : (MODE == MODE_B1_STORE || MODE == MODE_B1F_STORE) ? 24
-                                : fe                                                ? 40
-                                : full4                                             ? 25
-                                                                                    : 16;
+    // the sums a pair adds into, the staged record and the accumulators
+    static constexpr int sums = (MODE == MODE_MONO_HALO)    ? SUMS_MONO
+                                : (MODE == MODE_B1_STORE)   ? SUMS_T4
+                                : (MODE == MODE_B1F_STORE)  ? SUMS_X4T
+                                : (MODE == MODE_FULL_STORE) ? SUMS_X3
+                                : fe                        ? SUMS_FE
+                                : full4                     ? SUMS_X4
+                                                            : SUMS_F3;
+    static constexpr int nc = record_size(sums);
+    static constexpr int nacc = sums_count(sums);
 };
 
 // LDS plane layout: cell-major, Layout::stride doubles per cell -- the
-// centre (x, y, z), then the nq scaled source components, then padding. A
-// pair is read with 16-byte loads from one base address (immediate offsets).
+// source record (stage_record of ot_pair.h), then padding. A pair is read with
+// 16-byte loads from one base address (immediate offsets).
 // The cell stride in 16-byte units is odd, so the 8 lanes served per LDS
 // cycle by a 16-byte read -- 8 different cells modulo 8 in the mirrored lane
 // pattern -- fall on disjoint banks.
@@ -570,34 +346,15 @@ constexpr int lds_doubles()
 // (the block is wavefront-uniform, so its relation is a scalar load), loads
 // the cell's centre and each of its moments once (a load of a wavefront reads
 // 512 contiguous bytes in the batched forms, 8 rows of 64 bytes in the
-// single-block form), forms the scaled trace-reduced sources with
+// single-block form), forms the source record with
 // compile-time factors, and writes the cell's record with 16-byte LDS
 // stores. A missing neighbour block is staged far away with zero sources.
-template <int MODE, int B>
-__device__ __forceinline__ double staged_source(const double* raw)
-{
-    constexpr bool rev = ModeTraits<MODE>::source_role;
-    constexpr int cP = kRedP[B], cS = kRedS[B];
-    constexpr double aP = rev ? parity_sign(cP) : parity_sign(cP) * inv_multi_factorial(cP);
-    if constexpr (cS < 0) {
-        return raw[cP] * aP;
-    } else {
-        constexpr double aS = rev ? parity_sign(cS) : parity_sign(cS) * inv_multi_factorial(cS);
-        return __builtin_fma(raw[cS], -aS, raw[cP] * aP);
-    }
-}
-template <int MODE, int... B>
-__device__ __forceinline__ void staged_sources(const double* raw, double* val, std::integer_sequence<int, B...>)
-{
-    ((val[3 + B] = staged_source<MODE, B>(raw)), ...);
-}
-
 template <int MODE, int NW>
 __device__ __forceinline__ void stage_plane(const KParams& p, const int4* rel, int zs, int tid, double* lds)
 {
     using T = ModeTraits<MODE>;
     using Lay = Layout<MODE>;
-    constexpr int nm = (T::nq == 1) ? 1 : 20;  // moments read per cell
+    constexpr int nm = T::sums == SUMS_MONO ? 1 : 20;  // moments read per cell
     for (int v = tid; v < 9 * 64; v += NW * 64) {
         const int bxy = __builtin_amdgcn_readfirstlane(v >> 6);
         const int lane = v & 63;
@@ -632,7 +389,7 @@ __device__ __forceinline__ void stage_plane(const KParams& p, const int4* rel, i
             for (int c = 0; c < nm; ++c) raw[c] = pm[c * sm];
 #pragma unroll
             for (int k = 0; k < 3; ++k) val[k] = px[k * sx] + sh[k];
-            staged_sources<MODE>(raw, val, std::make_integer_sequence<int, T::nq>{});
+            stage_record<T::sums, T::source_role>(raw, val);
         } else {
 #pragma unroll
             for (int k = 0; k < 3; ++k) val[k] = kFar;
@@ -783,50 +540,7 @@ __global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
                         f[2 * j] = v.x;
                         f[2 * j + 1] = v.y;
                     }
-                    const double rx = xi - f[0];
-                    const double ry = yi - f[1];
-                    const double rz = zi - f[2];
-                    const double* q = f + 3;
-                    if constexpr (MODE == MODE_MONO_HALO) {
-                        double G[20];
-                        green<3>(rx, ry, rz, G);
-#pragma unroll
-                        for (int a = 0; a < 20; ++a) acc[a] = __builtin_fma(q[0], G[a], acc[a]);
-                    } else if constexpr (MODE == MODE_FULL_STORE) {
-                        // L_a, |a| <= 3 and |b| <= 3
-                        double D[7];
-                        radial<6>(rx, ry, rz, D);
-                        const double rr[3] = {rx, ry, rz};
-                        contract_full<0>(acc, q, rr, D, std::make_integer_sequence<int, 20>{});
-                    } else if constexpr (MODE == MODE_B1F_STORE) {
-                        // L'_g, 1 <= |g| <= 4, every |b| <= 3
-                        double D[8];
-                        radial<7>(rx, ry, rz, D);
-                        const double rr[3] = {rx, ry, rz};
-                        contract_full<1>(acc, q, rr, D, std::make_integer_sequence<int, 34>{});
-                    } else if constexpr (T::full4) {
-                        // C_d, 0 <= |d| <= 4, every source moment (|a| <= 3 or |b| <= 3)
-                        double D[8];
-                        radial<7>(rx, ry, rz, D);
-                        const double rr[3] = {rx, ry, rz};
-                        contract_full<0>(acc, q, rr, D, std::make_integer_sequence<int, 35>{});
-                    } else if constexpr (!T::adjoint && !T::fe) {
-                        // L_a, |a| + |b| <= 3
-                        double G[20];
-                        green<3>(rx, ry, rz, G);
-                        contract_red<0, TRUNC3>(acc, q, G, std::make_integer_sequence<int, 20>{});
-                    } else if constexpr (MODE == MODE_B1_STORE) {
-                        // L'_g, 1 <= |g| <= 4, |g| + |b| <= 4
-                        double G[35];
-                        green<4>(rx, ry, rz, G);
-                        contract_red<1, TRUNC4>(acc, q, G, std::make_integer_sequence<int, 34>{});
-                    } else {
-                        // F_d (|d| + |a| <= 3) and E_d (|d| + |a| = 4, |d| >= 1)
-                        double G[35];
-                        green<4>(rx, ry, rz, G);
-                        contract_red<0, TRUNC3>(acc, q, G, std::make_integer_sequence<int, 20>{});
-                        contract_red<1, EXACT4>(acc + 16, q, G, std::make_integer_sequence<int, 34>{});
-                    }
+                    pair_sums<T::sums>(acc, f, xi - f[0], yi - f[1], zi - f[2]);
                 }
             }
         }
@@ -864,6 +578,7 @@ __global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
         }
         if (half == 1) continue;  // the next pass (none after the last)
     }
+    finish_sums<T::sums>(acc);
     if constexpr (MODE == MODE_FSF_STORE) {
         // full truncation: L is the sums of orders 0..3 (kept slots 0..15);
         // the target-role sums C'_g, 1 <= |g| <= 4, are the kept slots 1..24
@@ -909,12 +624,7 @@ __global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
         for (int k = 0; k < 3; ++k) p.out1[k * p.out_stride + ob] = -gx[k];
     } else if constexpr (!T::adjoint) {
         double L[20];
-        if constexpr (MODE == MODE_MONO_HALO) {
-#pragma unroll
-            for (int a = 0; a < 20; ++a) L[a] = acc[a];
-        } else {
-            expand<0>(acc, L, std::make_integer_sequence<int, 20>{});
-        }
+        expand<0>(acc, L, std::make_integer_sequence<int, 20>{});
         if constexpr (T::halo) {
 #pragma unroll
             for (int a = 0; a < 20; ++a) p.out0[a * kSub3 + cell] = L[a];
