@@ -52,6 +52,7 @@
 #include "ot_host.h"
 #include "ot_fmm.h"
 #include "ot_interact.h"
+#include "ot_cells.h"
 #include "ot_coarse.h"
 
 namespace {
@@ -101,11 +102,23 @@ int ensure_device()
 namespace {
 
 
-template <int MODE, int NW, bool SPLIT = false, int NP = 1, bool PERSIST = false>
+template <int MODE, int NW, int NP = 1, bool PERSIST = false>
 int launch(const KParams& kp, int nblocks, hipStream_t stream)
 {
     if (nblocks <= 0) return OT_FMM_OK;
-    hipLaunchKernelGGL((k_interact<MODE, NW, SPLIT, NP, PERSIST>), dim3(nblocks), dim3(NW * 64), 0, stream,
+    hipLaunchKernelGGL((k_interact<MODE, NW, NP, PERSIST>), dim3(nblocks), dim3(NW * 64), 0, stream,
+                       kp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "kernel launch");
+    return OT_FMM_OK;
+}
+
+// The target cells of `owners` owners by k_cells.
+template <int MODE>
+int launch_cells(const KParams& kp, int owners, hipStream_t stream)
+{
+    constexpr int kt = cells_per_group<MODE>();
+    hipLaunchKernelGGL((k_cells<MODE, kt>), dim3((unsigned)owners * (kSub3 / kt)), dim3(kCellsThreads), 0, stream,
                        kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
@@ -260,7 +273,7 @@ int resident_per_cu()
 {
     static const int n = [] {
         int b = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, NW, false, NP, true>, NW * 64, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, NW, NP, true>, NW * 64, 0) !=
                 hipSuccess ||
             b < 1)
             b = 1;
@@ -328,8 +341,8 @@ int launch_timed(ot_fmm_plan plan, int which, KParams kp, int nblocks, bool pers
         const long resident = (long)plan->n_cu * resident_per_cu<MODE, NW, NP>();
         nblocks = (int)std::min<long>(nblocks, resident);
     }
-    rc = persistent ? launch<MODE, NW, false, NP, true>(kp, nblocks, stream)
-                    : launch<MODE, NW, false, NP, false>(kp, nblocks, stream);
+    rc = persistent ? launch<MODE, NW, NP, true>(kp, nblocks, stream)
+                    : launch<MODE, NW, NP, false>(kp, nblocks, stream);
     if (rc) return rc;
     return timing_end(ev, stream);
 }
@@ -958,8 +971,10 @@ int ot_fmm_monopole(const double* mass, const double* com, double* L, void* stre
     KParams kp{};
     kp.mom = mass;
     kp.pos = com;
+    kp.mom_stride = kp.pos_stride = kHalo3;
     kp.out0 = L;
-    return launch<MODE_MONO_HALO, 8, true>(kp, kSub, (hipStream_t)stream);
+    kp.out_stride = kSub3;
+    return launch_cells<MODE_MONO_HALO>(kp, 1, (hipStream_t)stream);
 }
 
 int ot_fmm_multipole(const double* M, const double* com, double* L, void* stream)
@@ -974,8 +989,10 @@ int ot_fmm_multipole(const double* M, const double* com, double* L, void* stream
     KParams kp{};
     kp.mom = M;
     kp.pos = com;
+    kp.mom_stride = kp.pos_stride = kHalo3;
     kp.out0 = L;
-    return launch<MODE_FWD_HALO, 8, true>(kp, kSub, (hipStream_t)stream);
+    kp.out_stride = kSub3;
+    return launch_cells<MODE_FWD_HALO>(kp, 1, (hipStream_t)stream);
 }
 
 int ot_fmm_plan_create(int32_t S, int32_t T, const int32_t* tgt, const int32_t* nbr,
@@ -1897,7 +1914,7 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
     kp.npieces = 0;
     const long resident = (long)ncu * resident_per_cu<MODE_FWD_STORE, 16, 1>();
     const int nblocks = (int)std::min<long>(T, resident);
-    if ((rc = launch<MODE_FWD_STORE, 16, false, 1, true>(kp, nblocks, s))) return rc;
+    if ((rc = launch<MODE_FWD_STORE, 16, 1, true>(kp, nblocks, s))) return rc;
     hipLaunchKernelGGL(k_noalloc_poison, dim3(1024), dim3(256), 0, s, head + 16, L, (long)(20 * NT));
     e = hipGetLastError();
     return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");

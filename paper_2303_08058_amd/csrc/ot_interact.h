@@ -319,265 +319,12 @@ struct ModeTraits {
     static constexpr int nacc = sums_count(sums);
 };
 
-// LDS plane layout: cell-major, Layout::stride doubles per cell -- the
-// source record (stage_record of ot_pair.h), then padding. A pair is read with
-// 16-byte loads from one base address (immediate offsets).
-// The cell stride in 16-byte units is odd, so the 8 lanes served per LDS
-// cycle by a 16-byte read -- 8 different cells modulo 8 in the mirrored lane
-// pattern -- fall on disjoint banks.
+// What a target cell's finished sums become: the outputs of the mode, written
+// (B1: added) at the cell's place. `acc`: the sums of cell `cell` of `owner`.
 template <int MODE>
-struct Layout {
-    static constexpr int nc = ModeTraits<MODE>::nc;
-    static constexpr int nvec = (nc + 1) / 2;                               // 16-byte reads per cell
-    static constexpr int stride = (nvec % 2 == 1) ? 2 * nvec : 2 * nvec + 2;  // doubles per cell
-};
-
-template <int MODE, int NW, bool SPLIT, int NP>
-constexpr int lds_doubles()
-{
-    constexpr int plane = Layout<MODE>::stride * kPlane;
-    constexpr int merge =
-        SPLIT ? NW * ModeTraits<MODE>::nacc * 64 : ((NW == 16 || NP == 2) ? 20 * kSub3 : 0);
-    return plane > merge ? plane : merge;
-}
-
-// Staging of one source z-plane (the 24 x 24 cells of the 3 x 3 neighbour
-// blocks), one cell per thread: thread v takes cell v & 63 of block v >> 6
-// (the block is wavefront-uniform, so its relation is a scalar load), loads
-// the cell's centre and each of its moments once (a load of a wavefront reads
-// 512 contiguous bytes in the batched forms, 8 rows of 64 bytes in the
-// single-block form), forms the source record with
-// compile-time factors, and writes the cell's record with 16-byte LDS
-// stores. A missing neighbour block is staged far away with zero sources.
-template <int MODE, int NW>
-__device__ __forceinline__ void stage_plane(const KParams& p, const int4* rel, int zs, int tid, double* lds)
+__device__ __forceinline__ void store_sums(const KParams& p, int owner, int cell, double* acc)
 {
     using T = ModeTraits<MODE>;
-    using Lay = Layout<MODE>;
-    constexpr int nm = T::sums == SUMS_MONO ? 1 : 20;  // moments read per cell
-    for (int v = tid; v < 9 * 64; v += NW * 64) {
-        const int bxy = __builtin_amdgcn_readfirstlane(v >> 6);
-        const int lane = v & 63;
-        const int by = bxy / 3, bx = bxy - 3 * by;
-        const double* pm;
-        const double* px;
-        long sm, sx;
-        double sh[3] = {0.0, 0.0, 0.0};
-        bool present = true;
-        if constexpr (T::halo) {
-            const long off = (long)zs * kPlane + (by * 8 + (lane >> 3)) * kHalo + bx * 8 + (lane & 7);
-            pm = p.mom + off;
-            px = p.pos + off;
-            sm = sx = kHalo3;
-        } else {
-            const int4 rr = rel[9 * (zs >> 3) + bxy];  // uniform address: scalar load
-            present = rr.x >= 0;
-            const long o = 64 * (zs & 7) + lane;
-            pm = p.mom + (present ? (long)rr.x * kSub3 : 0) + o;
-            px = p.pos + (present ? (long)rr.y * kSub3 : 0) + o;
-            sm = p.mom_stride;
-            sx = p.pos_stride;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) sh[k] = (double)(int)(int8_t)((rr.z >> (8 * k)) & 0xff) * p.period[k];
-        }
-        double val[2 * Lay::nvec];
-#pragma unroll
-        for (int c = 0; c < 2 * Lay::nvec; ++c) val[c] = 0.0;
-        if (present) {
-            double raw[nm];
-#pragma unroll
-            for (int c = 0; c < nm; ++c) raw[c] = pm[c * sm];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) val[k] = px[k * sx] + sh[k];
-            stage_record<T::sums, T::source_role>(raw, val);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) val[k] = kFar;
-        }
-        double2* dst = reinterpret_cast<double2*>(
-            lds + ((by * 8 + (lane >> 3)) * kHalo + bx * 8 + (lane & 7)) * Lay::stride);
-#pragma unroll
-        for (int j = 0; j < Lay::nvec; ++j) dst[j] = make_double2(val[2 * j], val[2 * j + 1]);
-    }
-}
-
-// SPLIT (single-block forms only): one work-group per target z-plane of the
-// block; its NW wavefronts share the plane's 64 cells and take the stencil
-// rows round-robin; only the 19 source planes within reach are staged, and the
-// partial sums are added in a fixed order at the end.
-// NP = 2 (8 wavefronts): two passes over the source planes, target planes
-// 0-3 then 4-7, two wavefronts per target plane with its stencil rows split
-// in halves as with 16 wavefronts. Each pass stages the 21 source planes in
-// its reach (42 instead of 24), and in exchange the work per staged plane is
-// spread evenly over the 4 SIMDs (about 95% against 86% for one pass with a
-// wavefront per target plane).
-template <int MODE, int NW, bool SPLIT, int NP, bool PERSIST>
-__global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
-{
-    using T = ModeTraits<MODE>;
-    using Lay = Layout<MODE>;
-    static_assert(NW == 8 || NW == 16, "8 or 16 wavefronts");
-    static_assert(!SPLIT || (T::halo && NW == 8 && NP == 1), "plane split: single-block forms, 8 wavefronts");
-    static_assert(NP == 1 || (NP == 2 && NW == 8), "two passes: 8 wavefronts");
-    constexpr bool HALVES = !SPLIT && (NW == 16 || NP == 2);  // two wavefronts per target plane
-    __shared__ double lds[lds_doubles<MODE, NW, SPLIT, NP>()];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = HALVES ? (wave & 1) : 0;
-    // Persistent launch (counter != NULL): the work-group takes work-list
-    // entries from a global counter until the list is exhausted; otherwise it
-    // does the one entry of its index.
-    __shared__ int s_item;
-    static_assert(!PERSIST || !T::halo, "persistent launches: batched forms");
-    constexpr bool persistent = PERSIST;
-    int item = (int)blockIdx.x;
-    // in pieces: the work-group starts on the piece of its XCD (work-group b
-    // runs on XCD b mod npieces) and moves on to the next piece when that is
-    // exhausted, until every piece is (s_step: pieces left behind)
-    __shared__ int s_step;
-    if (persistent && tid == 0) s_step = 0;
-#pragma unroll 1
-    for (;;) {
-    if (persistent) {
-        __syncthreads();  // the previous entry is finished by every wavefront
-        if (tid == 0) {
-            int it = p.n_items;
-            if (p.npieces > 0) {
-                for (int step = s_step; step < p.npieces; ++step) {
-                    const int k = ((int)blockIdx.x + step) % p.npieces;
-                    const int i = atomicAdd(p.counter + k, 1);
-                    if (i < p.piece_off[k + 1] - p.piece_off[k]) {
-                        it = p.piece_off[k] + i;
-                        s_step = step;
-                        break;
-                    }
-                }
-            } else {
-                it = atomicAdd(p.counter, 1);
-            }
-            s_item = it;
-        }
-        __syncthreads();
-        item = __builtin_amdgcn_readfirstlane(s_item);
-        if (item >= p.n_items) break;
-    }
-    const int owner = SPLIT ? 0 : (p.order ? p.order[item] : item);
-    const int4* s_rel = T::halo ? nullptr : p.rel + (long)owner * 27;  // this owner's relations
-#pragma unroll 1
-    for (int pass = 0; pass < NP; ++pass) {
-    // With 8 wavefronts and one pass (wave w on SIMD w % 4) the target planes
-    // are paired per SIMD as (0,4) (1,6) (2,5) (3,7): the pairing whose summed
-    // per-plane work varies least from one staged plane to the next.
-    const int zt = SPLIT ? (int)blockIdx.x
-                 : (NW == 16) ? (wave >> 1)
-                 : (NP == 2) ? 4 * pass + (wave >> 1)
-                             : (wave == 5 ? 6 : (wave == 6 ? 5 : wave));
-    const int xt = lane & 7, yt = lane >> 3;
-    const int pz = zt & 1;
-    const int cell = xt + 8 * yt + 64 * zt;
-    const int sgx = (xt & 1) ? -1 : 1;
-    const int sgy = (yt & 1) ? -1 : 1;
-
-    double xi, yi, zi;
-    if constexpr (T::halo) {
-        const int h = (8 + xt) + kHalo * (8 + yt) + kPlane * (8 + zt);
-        xi = p.pos[h];
-        yi = p.pos[kHalo3 + h];
-        zi = p.pos[2 * kHalo3 + h];
-    } else {
-        const long b = p.own_blk ? p.own_blk[owner] : owner;
-        const long o = b * kSub3 + cell;
-        xi = p.pos[o];
-        yi = p.pos[p.pos_stride + o];
-        zi = p.pos[2 * p.pos_stride + o];
-    }
-
-    double acc[T::nacc];
-#pragma unroll
-    for (int a = 0; a < T::nacc; ++a) acc[a] = 0.0;
-
-    // addresses in 16-byte units of the LDS plane
-    constexpr int cs = Lay::stride / 2;
-    const int lane_off = ((8 + yt) * kHalo + 8 + xt) * cs;
-    const int step_x = sgx * cs;
-    const int step_y = sgy * kHalo * cs;
-    const double2* lds2 = reinterpret_cast<const double2*>(lds);
-
-    const int zs_begin = SPLIT ? (8 + zt - kReach > 0 ? 8 + zt - kReach : 0)
-                       : (NP == 2 ? (pass == 0 ? 0 : 8 + 4 - kReach) : 0);
-    const int zs_end = SPLIT ? (8 + zt + kReach + 1 < kHalo ? 8 + zt + kReach + 1 : kHalo)
-                     : (NP == 2 ? (pass == 0 ? 8 + 3 + kReach + 1 : kHalo) : kHalo);
-    for (int zs = zs_begin; zs < zs_end; ++zs) {
-        __syncthreads();
-        stage_plane<MODE, NW>(p, s_rel, zs, tid, lds);
-        __syncthreads();
-        const int dz = zs - (8 + zt);
-        if (dz >= -kReach && dz <= kReach) {
-            const int* rg = c_stencil.range[pz][dz + kReach];
-            int r0 = rg[0], r1 = rg[2], rstep = 1;
-            if (SPLIT) {
-                r0 += wave;
-                rstep = NW;
-            } else if (HALVES) {
-                if (half == 0)
-                    r1 = rg[1];
-                else
-                    r0 = rg[1];
-            }
-            for (int r = r0; r < r1; r += rstep) {
-                const uint32_t w = c_stencil.rows[pz][r];
-                const int dy = (int)(int8_t)(w & 0xff);
-                const int dx0 = (int)(int8_t)((w >> 8) & 0xff);
-                const int n = (int)(w >> 16);
-                int off = lane_off + dy * step_y + dx0 * step_x;
-                for (int k = 0; k < n; ++k, off += step_x) {
-                    double f[2 * Lay::nvec];
-#pragma unroll
-                    for (int j = 0; j < Lay::nvec; ++j) {
-                        const double2 v = lds2[off + j];
-                        f[2 * j] = v.x;
-                        f[2 * j + 1] = v.y;
-                    }
-                    pair_sums<T::sums>(acc, f, xi - f[0], yi - f[1], zi - f[2]);
-                }
-            }
-        }
-    }
-
-    // ---------------- epilogues ----------------
-    if constexpr (SPLIT) {
-        // partial sums of the plane's wavefronts, added by wavefront 0 in order
-        __syncthreads();
-#pragma unroll
-        for (int a = 0; a < T::nacc; ++a) lds[(wave * T::nacc + a) * 64 + lane] = acc[a];
-        __syncthreads();
-        if (wave != 0) return;
-#pragma unroll
-        for (int a = 0; a < T::nacc; ++a) {
-            double v = lds[a * 64 + lane];
-            for (int w = 1; w < NW; ++w) v += lds[(w * T::nacc + a) * 64 + lane];
-            acc[a] = v;
-        }
-    } else if constexpr (HALVES) {
-        // the two wavefronts of a target plane add their partial sums, through
-        // LDS in rounds of at most 20 components
-#pragma unroll
-        for (int a0 = 0; a0 < T::nacc; a0 += 20) {
-            __syncthreads();
-            if (half == 1) {
-#pragma unroll
-                for (int a = a0; a < T::nacc && a < a0 + 20; ++a) lds[(a - a0) * kSub3 + cell] = acc[a];
-            }
-            __syncthreads();
-            if (half == 0) {
-#pragma unroll
-                for (int a = a0; a < T::nacc && a < a0 + 20; ++a) acc[a] += lds[(a - a0) * kSub3 + cell];
-            }
-        }
-        if (half == 1) continue;  // the next pass (none after the last)
-    }
     finish_sums<T::sums>(acc);
     if constexpr (MODE == MODE_FSF_STORE) {
         // full truncation: L is the sums of orders 0..3 (kept slots 0..15);
@@ -625,14 +372,9 @@ __global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
     } else if constexpr (!T::adjoint) {
         double L[20];
         expand<0>(acc, L, std::make_integer_sequence<int, 20>{});
-        if constexpr (T::halo) {
+        const long b = p.out_blk ? p.out_blk[owner] : owner;
 #pragma unroll
-            for (int a = 0; a < 20; ++a) p.out0[a * kSub3 + cell] = L[a];
-        } else {
-            const long b = p.out_blk ? p.out_blk[owner] : owner;
-#pragma unroll
-            for (int a = 0; a < 20; ++a) p.out0[a * p.out_stride + b * kSub3 + cell] = L[a];
-        }
+        for (int a = 0; a < 20; ++a) p.out0[a * p.out_stride + b * kSub3 + cell] = L[a];
     } else {
         double C[34];
         double F[20];
@@ -687,6 +429,223 @@ __global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
             for (int k = 0; k < 3; ++k) p.out0[k * p.out_stride + ob] += gx[k];
         }
     }
+}
+
+// LDS plane layout: cell-major, Layout::stride doubles per cell -- the
+// source record (stage_record of ot_pair.h), then padding. A pair is read with
+// 16-byte loads from one base address (immediate offsets).
+// The cell stride in 16-byte units is odd, so the 8 lanes served per LDS
+// cycle by a 16-byte read -- 8 different cells modulo 8 in the mirrored lane
+// pattern -- fall on disjoint banks.
+template <int MODE>
+struct Layout {
+    static constexpr int nc = ModeTraits<MODE>::nc;
+    static constexpr int nvec = (nc + 1) / 2;                               // 16-byte reads per cell
+    static constexpr int stride = (nvec % 2 == 1) ? 2 * nvec : 2 * nvec + 2;  // doubles per cell
+};
+
+template <int MODE, int NW, int NP>
+constexpr int lds_doubles()
+{
+    constexpr int plane = Layout<MODE>::stride * kPlane;
+    constexpr int merge = (NW == 16 || NP == 2) ? 20 * kSub3 : 0;
+    return plane > merge ? plane : merge;
+}
+
+// Staging of one source z-plane (the 24 x 24 cells of the 3 x 3 neighbour
+// blocks), one cell per thread: thread v takes cell v & 63 of block v >> 6
+// (the block is wavefront-uniform, so its relation is a scalar load), loads
+// the cell's centre and each of its moments once (a load of a wavefront reads
+// 512 contiguous bytes), forms the source record with
+// compile-time factors, and writes the cell's record with 16-byte LDS
+// stores. A missing neighbour block is staged far away with zero sources.
+template <int MODE, int NW>
+__device__ __forceinline__ void stage_plane(const KParams& p, const int4* rel, int zs, int tid, double* lds)
+{
+    using T = ModeTraits<MODE>;
+    using Lay = Layout<MODE>;
+    for (int v = tid; v < 9 * 64; v += NW * 64) {
+        const int bxy = __builtin_amdgcn_readfirstlane(v >> 6);
+        const int lane = v & 63;
+        const int by = bxy / 3, bx = bxy - 3 * by;
+        const int4 rr = rel[9 * (zs >> 3) + bxy];  // uniform address: scalar load
+        const bool present = rr.x >= 0;
+        const long o = 64 * (zs & 7) + lane;
+        const double* pm = p.mom + (present ? (long)rr.x * kSub3 : 0) + o;
+        const double* px = p.pos + (present ? (long)rr.y * kSub3 : 0) + o;
+        const long sm = p.mom_stride, sx = p.pos_stride;
+        double sh[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) sh[k] = (double)(int)(int8_t)((rr.z >> (8 * k)) & 0xff) * p.period[k];
+        double val[2 * Lay::nvec];
+#pragma unroll
+        for (int c = 0; c < 2 * Lay::nvec; ++c) val[c] = 0.0;
+        if (present) {
+            double raw[20];
+#pragma unroll
+            for (int c = 0; c < 20; ++c) raw[c] = pm[c * sm];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) val[k] = px[k * sx] + sh[k];
+            stage_record<T::sums, T::source_role>(raw, val);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) val[k] = kFar;
+        }
+        double2* dst = reinterpret_cast<double2*>(
+            lds + ((by * 8 + (lane >> 3)) * kHalo + bx * 8 + (lane & 7)) * Lay::stride);
+#pragma unroll
+        for (int j = 0; j < Lay::nvec; ++j) dst[j] = make_double2(val[2 * j], val[2 * j + 1]);
+    }
+}
+
+// NP = 2 (8 wavefronts): two passes over the source planes, target planes
+// 0-3 then 4-7, two wavefronts per target plane with its stencil rows split
+// in halves as with 16 wavefronts. Each pass stages the 21 source planes in
+// its reach (42 instead of 24), and in exchange the work per staged plane is
+// spread evenly over the 4 SIMDs (about 95% against 86% for one pass with a
+// wavefront per target plane).
+template <int MODE, int NW, int NP, bool PERSIST>
+__global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
+{
+    using T = ModeTraits<MODE>;
+    using Lay = Layout<MODE>;
+    static_assert(NW == 8 || NW == 16, "8 or 16 wavefronts");
+    static_assert(NP == 1 || (NP == 2 && NW == 8), "two passes: 8 wavefronts");
+    constexpr bool HALVES = NW == 16 || NP == 2;  // two wavefronts per target plane
+    __shared__ double lds[lds_doubles<MODE, NW, NP>()];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = HALVES ? (wave & 1) : 0;
+    // Persistent launch (counter != NULL): the work-group takes work-list
+    // entries from a global counter until the list is exhausted; otherwise it
+    // does the one entry of its index.
+    __shared__ int s_item;
+    constexpr bool persistent = PERSIST;
+    int item = (int)blockIdx.x;
+    // in pieces: the work-group starts on the piece of its XCD (work-group b
+    // runs on XCD b mod npieces) and moves on to the next piece when that is
+    // exhausted, until every piece is (s_step: pieces left behind)
+    __shared__ int s_step;
+    if (persistent && tid == 0) s_step = 0;
+#pragma unroll 1
+    for (;;) {
+    if (persistent) {
+        __syncthreads();  // the previous entry is finished by every wavefront
+        if (tid == 0) {
+            int it = p.n_items;
+            if (p.npieces > 0) {
+                for (int step = s_step; step < p.npieces; ++step) {
+                    const int k = ((int)blockIdx.x + step) % p.npieces;
+                    const int i = atomicAdd(p.counter + k, 1);
+                    if (i < p.piece_off[k + 1] - p.piece_off[k]) {
+                        it = p.piece_off[k] + i;
+                        s_step = step;
+                        break;
+                    }
+                }
+            } else {
+                it = atomicAdd(p.counter, 1);
+            }
+            s_item = it;
+        }
+        __syncthreads();
+        item = __builtin_amdgcn_readfirstlane(s_item);
+        if (item >= p.n_items) break;
+    }
+    const int owner = p.order ? p.order[item] : item;
+    const int4* s_rel = p.rel + (long)owner * 27;  // this owner's relations
+#pragma unroll 1
+    for (int pass = 0; pass < NP; ++pass) {
+    // With 8 wavefronts and one pass (wave w on SIMD w % 4) the target planes
+    // are paired per SIMD as (0,4) (1,6) (2,5) (3,7): the pairing whose summed
+    // per-plane work varies least from one staged plane to the next.
+    const int zt = (NW == 16) ? (wave >> 1)
+                 : (NP == 2) ? 4 * pass + (wave >> 1)
+                             : (wave == 5 ? 6 : (wave == 6 ? 5 : wave));
+    const int xt = lane & 7, yt = lane >> 3;
+    const int pz = zt & 1;
+    const int cell = xt + 8 * yt + 64 * zt;
+    const int sgx = (xt & 1) ? -1 : 1;
+    const int sgy = (yt & 1) ? -1 : 1;
+
+    double xi, yi, zi;
+    {
+        const long b = p.own_blk ? p.own_blk[owner] : owner;
+        const long o = b * kSub3 + cell;
+        xi = p.pos[o];
+        yi = p.pos[p.pos_stride + o];
+        zi = p.pos[2 * p.pos_stride + o];
+    }
+
+    double acc[T::nacc];
+#pragma unroll
+    for (int a = 0; a < T::nacc; ++a) acc[a] = 0.0;
+
+    // addresses in 16-byte units of the LDS plane
+    constexpr int cs = Lay::stride / 2;
+    const int lane_off = ((8 + yt) * kHalo + 8 + xt) * cs;
+    const int step_x = sgx * cs;
+    const int step_y = sgy * kHalo * cs;
+    const double2* lds2 = reinterpret_cast<const double2*>(lds);
+
+    const int zs_begin = NP == 2 ? (pass == 0 ? 0 : 8 + 4 - kReach) : 0;
+    const int zs_end = NP == 2 ? (pass == 0 ? 8 + 3 + kReach + 1 : kHalo) : kHalo;
+    for (int zs = zs_begin; zs < zs_end; ++zs) {
+        __syncthreads();
+        stage_plane<MODE, NW>(p, s_rel, zs, tid, lds);
+        __syncthreads();
+        const int dz = zs - (8 + zt);
+        if (dz >= -kReach && dz <= kReach) {
+            const int* rg = c_stencil.range[pz][dz + kReach];
+            int r0 = rg[0], r1 = rg[2];
+            if (HALVES) {
+                if (half == 0)
+                    r1 = rg[1];
+                else
+                    r0 = rg[1];
+            }
+            for (int r = r0; r < r1; ++r) {
+                const uint32_t w = c_stencil.rows[pz][r];
+                const int dy = (int)(int8_t)(w & 0xff);
+                const int dx0 = (int)(int8_t)((w >> 8) & 0xff);
+                const int n = (int)(w >> 16);
+                int off = lane_off + dy * step_y + dx0 * step_x;
+                for (int k = 0; k < n; ++k, off += step_x) {
+                    double f[2 * Lay::nvec];
+#pragma unroll
+                    for (int j = 0; j < Lay::nvec; ++j) {
+                        const double2 v = lds2[off + j];
+                        f[2 * j] = v.x;
+                        f[2 * j + 1] = v.y;
+                    }
+                    pair_sums<T::sums>(acc, f, xi - f[0], yi - f[1], zi - f[2]);
+                }
+            }
+        }
+    }
+
+    // ---------------- epilogues ----------------
+    if constexpr (HALVES) {
+        // the two wavefronts of a target plane add their partial sums, through
+        // LDS in rounds of at most 20 components
+#pragma unroll
+        for (int a0 = 0; a0 < T::nacc; a0 += 20) {
+            __syncthreads();
+            if (half == 1) {
+#pragma unroll
+                for (int a = a0; a < T::nacc && a < a0 + 20; ++a) lds[(a - a0) * kSub3 + cell] = acc[a];
+            }
+            __syncthreads();
+            if (half == 0) {
+#pragma unroll
+                for (int a = a0; a < T::nacc && a < a0 + 20; ++a) acc[a] += lds[(a - a0) * kSub3 + cell];
+            }
+        }
+        if (half == 1) continue;  // the next pass (none after the last)
+    }
+    store_sums<MODE>(p, owner, cell, acc);
     }  // pass
     if (!persistent) break;
     }  // work-list entries
