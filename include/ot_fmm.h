@@ -58,28 +58,29 @@ enum {
     OT_FMM_ETIMEDOUT = -5     /* ot_fmm_future_wait: not ready within the limit */
 };
 
-/* Schedules (how a target sub-grid's 512 cells are spread over wavefronts).
- * All keep one work-group per target sub-grid and one staged source z-plane
- * in LDS; lanes are the 8x8 target cells of one z-plane.
+/* Schedules: a shape, optionally with flags for how its work is launched.
+ * The library splits the work over wavefronts by the pass and the number of
+ * targets; the three shapes are accepted where they always were and select
+ * that same split, so results do not depend on the schedule.
  * The adjoint takes two: sched = target_role | (source_role << 8)
  * (OT_FMM_SCHED_BWD); the target-role pass accepts every schedule, the
- * source-role pass AUTO, W8 or W8P2 (its accumulators do not fit 16
- * wavefronts). A byte left AUTO takes the plan's tuned choice, else W16 for
- * the target role and W8 for the source role. */
+ * source-role pass AUTO, W8 or W8P2. A byte left AUTO takes the plan's tuned
+ * choice, else PERSISTENT | LOCAL from 640 targets (source role: store
+ * sub-grids) on and no flags below; where AUTO finds no work counters left
+ * (below) it drops PERSISTENT. */
 enum {
-    OT_FMM_SCHED_AUTO = 0,  /* the plan's tuned choice (ot_fmm_autotune), else W16 */
-    OT_FMM_SCHED_W8 = 1,    /* 8 wavefronts: one per target z-plane */
-    OT_FMM_SCHED_W16 = 2,   /* 16 wavefronts: two per target z-plane, stencil rows split */
-    OT_FMM_SCHED_W8P2 = 3,  /* 8 wavefronts, two passes over the source planes (target
-                               planes 0-3, then 4-7), two wavefronts per target plane */
+    OT_FMM_SCHED_AUTO = 0,  /* the plan's tuned choice (ot_fmm_autotune), else as above */
+    OT_FMM_SCHED_W8 = 1,
+    OT_FMM_SCHED_W16 = 2,
+    OT_FMM_SCHED_W8P2 = 3,
     /* flag, OR-ed into a schedule: persistent launch -- as many work-groups as
      * are resident at once, taking work-list entries (longest first) from
-     * counters that a one-thread kernel zeroes just before, on the same
-     * stream. The counters are never shared by launches that can overlap:
-     * eager launches use one set per stream (up to 64 streams per plan),
-     * launches recorded into a graph a set of their own (up to 960 per plan
-     * over its life; the plan's own step graph returns its sets when it is
-     * replaced). Beyond either limit the call returns OT_FMM_EINVAL. */
+     * counters that every launch leaves at zero for the next one. The
+     * counters are never shared by launches that can overlap: eager launches
+     * use one set per stream (up to 64 streams per plan), launches recorded
+     * into a graph a set of their own (up to 960 per plan over its life; the
+     * plan's own step graph returns its sets when it is replaced). Beyond
+     * either limit the call returns OT_FMM_EINVAL. */
     OT_FMM_SCHED_PERSISTENT = 0x10,
     /* flag, OR-ed into a schedule: XCD-aware work order -- entries sorted
      * along a Morton curve of the lattice positions recovered from the
@@ -207,16 +208,15 @@ int ot_fmm_multipole_batched(ot_fmm_plan plan, const double* M, const double* co
  *   L_a(i) = sum_{j in S(i)} sum_{|b| <= 3} s_b M_b(j) G_{a+b}(X_i - X_j),
  * the alternative to the total-order truncation |a| + |b| <= 3 of
  * ot_fmm_multipole_batched (Sec. 2.1 names the FMM without its truncation;
- * this is the other reading). Same plan, layouts, schedules (AUTO = W8P2 |
- * PERSISTENT | LOCAL, not autotuned) and
- * error rules as ot_fmm_multipole_batched; L is overwritten. */
+ * this is the other reading). Same plan, layouts, schedules (not autotuned)
+ * and error rules as ot_fmm_multipole_batched; L is overwritten. */
 int ot_fmm_multipole_batched_full(ot_fmm_plan plan, const double* M, const double* com, double* L,
                                   int sched, void* stream);
 
 /* Adjoint of ot_fmm_multipole_batched_full (derivatives of G to order 7):
  * the same arrays, overwrite rules and errors as ot_fmm_multipole_backward;
- * schedules as there, AUTO = W8P2 | PERSISTENT | LOCAL for both passes, a target-role
- * shape of 16 wavefronts is EINVAL. */
+ * schedules as there, not autotuned; a target-role shape of 16 wavefronts is
+ * EINVAL. */
 int ot_fmm_multipole_backward_full(ot_fmm_plan plan, const double* M, const double* com,
                                    const double* gL, double* gM, double* gcom, int sched,
                                    void* stream);
@@ -247,7 +247,7 @@ int ot_fmm_multipole_backward(ot_fmm_plan plan, const double* M, const double* c
  *   of the same M and com: one pass over the store sub-grids (source role),
  *   whose cells add their own target role from Cs.
  * Schedules: W8 or W8P2 with the PERSISTENT / LOCAL flags, or AUTO (the
- * choice of ot_fmm_autotune_saved, else W8P2 | PERSISTENT | LOCAL); 16
+ * choice of ot_fmm_autotune_saved, else as for the other passes); 16
  * wavefronts are EINVAL. Errors and overlap rules as for the other batched
  * calls (Cs counts as an output of the forward and an input of the adjoint). */
 int ot_fmm_multipole_batched_save(ot_fmm_plan plan, const double* M, const double* com, double* L,
@@ -261,8 +261,8 @@ int ot_fmm_multipole_backward_saved(ot_fmm_plan plan, const double* M, const dou
  * s_b M_b(j) G_{g+b}(X_i - X_j), 1 <= |g| <= 4 (= dL_a(i)/dX_i,k under the full
  * truncation for g = a + e_k; its orders 1..3 equal L), the same 24 kept
  * components; derivatives of G to order 7. Schedules: W8 or W8P2 with the
- * flags, AUTO = W8P2 | PERSISTENT | LOCAL (not autotuned); errors and overlap
- * rules as for the total-order pair. */
+ * flags, or AUTO (not autotuned); errors and overlap rules as for the
+ * total-order pair. */
 int ot_fmm_multipole_batched_full_save(ot_fmm_plan plan, const double* M, const double* com, double* L,
                                        double* Cs, int sched, void* stream);
 int ot_fmm_multipole_backward_full_saved(ot_fmm_plan plan, const double* M, const double* com,
@@ -290,9 +290,8 @@ int ot_fmm_multipole_backward_full_saved(ot_fmm_plan plan, const double* M, cons
 int ot_fmm_multipole_batched_amc(ot_fmm_plan plan, const double* M, const double* com, double* L,
                                  double* dF, int sched, void* stream);
 
-/* Times both passes of the two-pass step with every schedule (W8, W8P2, each
- * with the four flag combinations) on the given buffers and keeps the fastest
- * in the plan (used by AUTO); leaves the results of the chosen schedules in
+/* Times both passes of the two-pass step with the four flag combinations on
+ * the given buffers and keeps the fastest in the plan (used by AUTO); leaves the results of the chosen schedules in
  * L, Cs, gM and gcom. Synchronizes `stream`; not while capturing. */
 int ot_fmm_autotune_saved(ot_fmm_plan plan, const double* M, const double* com, double* L,
                           double* Cs, const double* gL, double* gM, double* gcom, void* stream,
@@ -305,10 +304,10 @@ int ot_fmm_step_graph_create_saved(ot_fmm_plan plan, const double* M, const doub
                                    double* Cs, const double* gL, double* gM, double* gcom,
                                    int fwd_sched, int bwd_sched);
 
-/* Times every schedule of the forward (and backward, if gL/gM/gcom are not
- * NULL) on the given buffers and stores the fastest in the plan; returns the
- * choices. Every shape is timed with each combination of the persistent and
- * XCD-aware flags, the forward and the two adjoint passes each on its own.
+/* Times the forward (and backward, if gL/gM/gcom are not NULL) with each
+ * combination of the persistent and XCD-aware flags on the given buffers, the
+ * forward and the two adjoint passes each on its own, and stores the fastest
+ * in the plan; returns the choices.
  * Synchronizes `stream`; do not call it while capturing. The buffers are
  * overwritten with valid results (L of the last forward timed, gM and gcom
  * of one backward with the chosen schedules). */

@@ -48,8 +48,6 @@ static_assert(CellSources<1>::n == 1799, "stencil size");
 template <int KT>
 __constant__ CellSources<KT> c_cell_sources = build_cell_sources<KT>();
 
-constexpr int kCellsThreads = 512;
-
 // Target cells of a work-group: two where their accumulators (2 x 16) leave
 // room for a source's record and the pair step below 256 registers.
 template <int MODE>
@@ -82,20 +80,21 @@ __device__ __forceinline__ int lanes_sum(double* v, int lane, int base, int coun
     }
 }
 
-// One work-group of 8 wavefronts per KT target cells. A launch over few
-// targets leaves most of the chip idle when a work-group owns a whole
-// sub-grid (512 cells x 1799 sources); here a single sub-grid is 256 or 512
-// work-groups, each thread takes 4 sources straight from memory (a source
-// serves both cells of a pair), and the partial sums meet by lane exchange and
-// once through LDS. A thread's pair costs 23 loads instead of ten LDS reads
-// shared by nobody else, so the plane-staging kernel is faster once its
-// work-groups fill the chip.
-template <int MODE, int KT>
-__global__ void __launch_bounds__(kCellsThreads) k_cells(const KParams p)
+// One work-group of NT threads per KT target cells. A launch over few targets
+// leaves most of the chip idle when a work-group owns a plane of cells; here a
+// single sub-grid is 256 or 512 work-groups, each thread takes 4 (NT = 512) or
+// 8 sources straight from memory (a source serves both cells of a pair), and
+// the partial sums meet by lane exchange and once through LDS. One sub-grid,
+// forward: 10 us with 512 threads, 12 with 256 (145 with k_interact); with
+// saved sums: 17 and 14 (156). Per sub-grid of many: 11 us with 512 threads, 7
+// with 256, whose sums are merged half as often (k_interact on a full chip: 3.3,
+// since a staged source serves 64 targets there).
+template <int MODE, int KT, int NT>
+__global__ void __launch_bounds__(NT) k_cells(const KParams p)
 {
     using T = ModeTraits<MODE>;
     constexpr int kGroups = kSub3 / KT;
-    constexpr int kWaves = kCellsThreads / 64;
+    constexpr int kWaves = NT / 64;
     constexpr int kN = KT * T::nacc;
     __shared__ double s_sum[kWaves][kN];
     __shared__ int4 s_rel[27];
@@ -120,7 +119,7 @@ __global__ void __launch_bounds__(kCellsThreads) k_cells(const KParams p)
     double acc[kN];
 #pragma unroll
     for (int a = 0; a < kN; ++a) acc[a] = 0.0;
-    for (int i = tid; i < CellSources<KT>::n; i += kCellsThreads) {
+    for (int i = tid; i < CellSources<KT>::n; i += NT) {
         const uint32_t w = c_cell_sources<KT>.at[i];
         const int dx = (int)(int8_t)(w & 0xff), dy = (int)(int8_t)((w >> 8) & 0xff),
                   dz = (int)(int8_t)((w >> 16) & 0xff);

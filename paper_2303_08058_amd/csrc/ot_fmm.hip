@@ -10,19 +10,19 @@
 // stencil (|j-i| > 4 and |floor(j/2) - floor(i/2)| <= 4) inside the 24^3 halo.
 //
 // Design (CDNA4):
-//  * One work-group per target sub-grid (batched: per work-list entry). The
-//    24^3 halo (2.54 MB of FP64 for moments + centres) cannot sit in the
-//    160 KB LDS, so it streams through LDS one source z-plane at a time
-//    (24 x 24 cells x 23 components = 106 KB), read from HBM with coalesced
-//    512-byte rows.
-//  * A wavefront = the 64 cells of one target z-plane (lane = x + 8 y). The
-//    stencil depends only on the target's parity; the parities differing in
-//    x or y are mirror images of each other (the criterion is invariant
-//    under j -> 23 - j), so every lane walks the same per-z-parity offset
-//    table (a list of (dy, dx-interval) rows per dz) with its own x/y sign.
-//    Offsets are wave-uniform: no masking, scalar-unit loop control, and one
-//    VALU add per offset for the LDS address. Bank mapping of the 8x8 lane
-//    pattern with 24-wide rows is conflict-free for ds_read_b64.
+//  * Batched: a work-group of 4 wavefronts takes a part of a target sub-grid
+//    (a work-list entry), two work-groups a CU. The 24^3 halo (2.54 MB of FP64
+//    for moments + centres) cannot sit in the 160 KB LDS, so it streams
+//    through LDS one source z-plane at a time (the 448 of 24 x 24 cells in
+//    reach x 20 doubles = 70 KB), read from HBM with coalesced rows. Few
+//    targets: a work-group per one or two target cells instead (ot_cells.h).
+//  * A wavefront = the 64 cells of one target z-plane (lane = x + 8 y), or of
+//    two. The stencil depends only on the target's parity; the parities
+//    differing in x or y are mirror images of each other (the criterion is
+//    invariant under j -> 23 - j), so every lane walks the same offset table
+//    (a list of (dy, dx-interval) rows per dz) with its own x/y sign. Offsets
+//    are wave-uniform: no masking, scalar-unit loop control, and one VALU add
+//    per offset for the LDS address.
 //  * All arithmetic is FP64 VALU: per pair one rsqrt (v_rsq_f64 plus a
 //    third-order Newton correction), the radial factors D_n = (-1)^{n+1}
 //    (2n-1)!! / r^{2n+1}, and the contraction arranged around the separation
@@ -102,30 +102,50 @@ int ensure_device()
 namespace {
 
 
-template <int MODE, int NW, int NP = 1, bool PERSIST = false>
+template <int MODE, int RS, bool PERSIST>
 int launch(const KParams& kp, int nblocks, hipStream_t stream)
 {
     if (nblocks <= 0) return OT_FMM_OK;
-    hipLaunchKernelGGL((k_interact<MODE, NW, NP, PERSIST>), dim3(nblocks), dim3(NW * 64), 0, stream,
-                       kp);
+    hipLaunchKernelGGL((k_interact<MODE, RS, PERSIST>), dim3(nblocks), dim3(kThreads), 0, stream, kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return OT_FMM_OK;
 }
 
-// The target cells of `owners` owners by k_cells.
+// The target cells of `owners` owners by k_cells: 512 threads for the pairs of
+// cells of a single sub-grid (256 work-groups), else 256.
 template <int MODE>
 int launch_cells(const KParams& kp, int owners, hipStream_t stream)
 {
     constexpr int kt = cells_per_group<MODE>();
-    hipLaunchKernelGGL((k_cells<MODE, kt>), dim3((unsigned)owners * (kSub3 / kt)), dim3(kCellsThreads), 0, stream,
-                       kp);
+    const dim3 grid((unsigned)owners * (kSub3 / kt));
+    if (kt == 2 && owners == 1)
+        hipLaunchKernelGGL((k_cells<MODE, kt, kt == 2 ? 512 : 256>), grid, dim3(512), 0, stream, kp);
+    else if constexpr (!ModeTraits<MODE>::halo)
+        hipLaunchKernelGGL((k_cells<MODE, kt, 256>), grid, dim3(256), 0, stream, kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return OT_FMM_OK;
 }
 
-constexpr int kDefaultSourceSched = OT_FMM_SCHED_W8;
+// Up to this many targets (or store sub-grids) k_cells is faster than the
+// work-groups of k_interact, which do not fill the chip: forward of 27 (open
+// box) 191 us against 243, of 48 354 against 249; with saved sums 16 142
+// against 167, 27 374 against 260.
+template <int MODE>
+constexpr int cells_owners()
+{
+    return cells_per_group<MODE>() == 2 ? 32 : 18;
+}
+
+// Below this many targets (or store sub-grids), modes with a plane a wavefront
+// let four wavefronts share one (8 work-groups a target) instead of two.
+// Forward with saved sums of 27 targets: 294 us against 474 with two; 64: 494
+// against 496; 693: 4.89 against 4.58 ms.
+constexpr int kSplitOwners = 64;
+
+// Every shape selects the same kernel; the tuners try the flags on this one.
+constexpr int kTunedShape = OT_FMM_SCHED_W8;
 
 constexpr int kShapeMask = 0x0f;
 
@@ -150,36 +170,44 @@ bool valid_bwd_sched(int s)
 }
 
 // Work counters of persistent launches. Each launch takes a slot of
-// kMaxPieces counters that no launch able to run at the same time shares:
+// kMaxPieces counters that no launch able to run at the same time shares; the
+// launch leaves them zero (see k_interact), so a slot is ready for the next:
 //  * eager launches: one slot per stream -- launches on one stream run in
-//    order, each preceded on that stream by the kernel that zeroes its slot
-//    (kEagerSlots streams per plan);
+//    order (kEagerSlots streams per plan);
 //  * launches recorded into a graph (the stream is capturing): a slot of
 //    their own that no other launch is given, since the graph may be
 //    replayed at any time until it is destroyed, which the library cannot
 //    see (kCaptureSlots per plan); the slots of the plan's own step graph
 //    return to the pool when that graph is replaced.
+// Launches that AUTO makes persistent have a pool of the same size of their
+// own, and run as ordinary launches once it is used up: they never take a
+// slot from a launch whose schedule asks for one.
 constexpr int kEagerSlots = 64;
 constexpr int kCaptureSlots = 960;
-constexpr int kCounterSlots = kEagerSlots + kCaptureSlots;
+constexpr int kPoolSlots = kEagerSlots + kCaptureSlots;
+constexpr int kCounterSlots = 2 * kPoolSlots;
 
-// default schedule of every full-truncation pass (not autotuned): 8
-// wavefronts in two passes, persistent, in the XCD-aware pieces -- measured
-// 6% faster than one pass of 8 wavefronts for the forward and the adjoint
-constexpr int kFullSched = OT_FMM_SCHED_W8P2 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL;
+// A schedule that AUTO stands for may be given up for an ordinary launch.
+constexpr int kOptional = 0x100;
 
-// default schedule of the forward with saved sums and of the one-pass adjoint
-// when the plan has not been tuned (their 40 accumulators rule out 16
-// wavefronts, as for the two-pass adjoint's source role)
-constexpr int kSaveSched = OT_FMM_SCHED_W8P2 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL;
+// AUTO of an untuned plan: persistent in the XCD-aware pieces from this many
+// targets (or store sub-grids) on, an ordinary launch, longest work first,
+// below. The pieces cut the staging traffic (forward of 16384 sub-grids 57.8
+// -> 52.6 ms, 4096: 14.2 -> 13.4); with few work-groups a CU they end less
+// evenly (512: 1.69 -> 1.83 ms).
+constexpr int kPersistentOwners = 640;
 
 // kernels timed by the plan's events (ot_fmm_plan_kernel_times)
 constexpr int kTimedKernels = OT_FMM_NKERNELS;
 
-int pick_fwd(int sched, int tuned)
+// The schedule of one pass over `owners` targets or store sub-grids.
+int pick(int sched, int tuned, int owners)
 {
-    if (sched == OT_FMM_SCHED_AUTO) sched = tuned ? tuned : OT_FMM_SCHED_W16;
-    return sched;
+    if (sched != OT_FMM_SCHED_AUTO) return sched;
+    if (tuned) return tuned;
+    return owners >= kPersistentOwners
+               ? (OT_FMM_SCHED_W8 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL | kOptional)
+               : OT_FMM_SCHED_W8;
 }
 
 }  // namespace
@@ -208,14 +236,16 @@ struct ot_fmm_plan_s {
     int rev_piece_off[kMaxPieces + 1] = {0};
     int tuned_fwd = 0, tuned_bwd = 0;
     int tuned_save = 0, tuned_saved_bwd = 0;  // forward with saved sums, one-pass adjoint
-    // persistent launches: kMaxPieces work counters per slot; slots
-    // [0, kEagerSlots) belong to streams (eager launches), the others to
-    // launches recorded into graphs (see counter_slot)
+    // persistent launches: kMaxPieces work counters per slot, two pools of
+    // slots (see counter_slot), in each [0, kEagerSlots) of streams (eager
+    // launches) and the others of launches recorded into graphs
     int* d_counters = nullptr;  // [kCounterSlots][kMaxPieces]
     std::mutex slot_mutex;
-    std::vector<std::pair<hipStream_t, int>> stream_slot;  // eager: stream -> slot
-    int next_capture = 0;                  // capture slots handed out so far
-    std::vector<int> free_capture;         // capture slots returned by replaced step graphs
+    struct SlotPool {
+        std::vector<std::pair<hipStream_t, int>> stream_slot;  // eager: stream -> slot
+        int next_capture = 0;           // capture slots handed out so far
+        std::vector<int> free_capture;  // capture slots returned by replaced step graphs
+    } pool[2];
     std::vector<int> graph_slots;          // capture slots of the plan's step graph
     std::vector<int>* capture_log = nullptr;  // collects them while it is captured
     hipStream_t capture_stream = nullptr;     // on this stream
@@ -268,13 +298,12 @@ int timing_end(const std::pair<hipEvent_t, hipEvent_t>& ev, hipStream_t stream)
 
 // Work-groups of one instantiation resident per CU (LDS and registers), from
 // the runtime's occupancy calculator, computed once.
-template <int MODE, int NW, int NP>
+template <int MODE, int RS>
 int resident_per_cu()
 {
     static const int n = [] {
         int b = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, NW, NP, true>, NW * 64, 0) !=
-                hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, RS, true>, kThreads, 0) != hipSuccess ||
             b < 1)
             b = 1;
         return b;
@@ -282,78 +311,81 @@ int resident_per_cu()
     return n;
 }
 
-// The counter slot of a persistent launch on `stream` (kEagerSlots /
-// kCaptureSlots rules above).
-int counter_slot(ot_fmm_plan plan, hipStream_t stream, int** out)
+// The counter slot of a persistent launch on `stream` (rules above); optional:
+// from the second pool, and *out stays NULL where that has none left.
+int counter_slot(ot_fmm_plan plan, hipStream_t stream, bool optional, int** out)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     OT_HIP(hipStreamIsCapturing(stream, &st));
     std::lock_guard<std::mutex> lock(plan->slot_mutex);
+    auto& pool = plan->pool[optional ? 1 : 0];
+    const int base = optional ? kPoolSlots : 0;
     int slot = -1;
     if (st != hipStreamCaptureStatusNone) {
-        if (!plan->free_capture.empty()) {
-            slot = plan->free_capture.back();
-            plan->free_capture.pop_back();
-        } else if (plan->next_capture < kCaptureSlots) {
-            slot = kEagerSlots + plan->next_capture++;
+        if (!pool.free_capture.empty()) {
+            slot = pool.free_capture.back();
+            pool.free_capture.pop_back();
+        } else if (pool.next_capture < kCaptureSlots) {
+            slot = base + kEagerSlots + pool.next_capture++;
+        } else if (optional) {
+            return OT_FMM_OK;
         } else {
             return fail(OT_FMM_EINVAL, "more persistent launches recorded into graphs than the plan's "
                                        "960 counter slots; use a non-persistent schedule or a new plan");
         }
         if (plan->capture_log && stream == plan->capture_stream) plan->capture_log->push_back(slot);
     } else {
-        for (const auto& e : plan->stream_slot)
+        for (const auto& e : pool.stream_slot)
             if (e.first == stream) {
                 slot = e.second;
                 break;
             }
         if (slot < 0) {
-            if ((int)plan->stream_slot.size() >= kEagerSlots)
+            if ((int)pool.stream_slot.size() >= kEagerSlots) {
+                if (optional) return OT_FMM_OK;
                 return fail(OT_FMM_EINVAL, "persistent launches of one plan on more than 64 streams; use a "
                                            "non-persistent schedule or another plan");
-            slot = (int)plan->stream_slot.size();
-            plan->stream_slot.emplace_back(stream, slot);
+            }
+            slot = base + (int)pool.stream_slot.size();
+            pool.stream_slot.emplace_back(stream, slot);
         }
     }
     *out = plan->d_counters + (size_t)slot * kMaxPieces;
     return OT_FMM_OK;
 }
 
-// One launch over `nblocks` work-list entries: a work-group per entry, or
-// (persistent) as many work-groups as fit the device at once, each taking
-// entries from a counter slot of the plan, zeroed just before on the stream.
-template <int MODE, int NW, int NP = 1>
-int launch_timed(ot_fmm_plan plan, int which, KParams kp, int nblocks, bool persistent,
-                 hipStream_t stream)
+// One launch of k_interact over all parts of `owners` targets (or store
+// sub-grids): a work-group per entry, or (counter given) as many work-groups as
+// fit the device at once, taking entries from it.
+template <int MODE, int RS>
+int launch_parts(KParams kp, int owners, int* counter, int n_cu, hipStream_t stream)
 {
-    int* c = nullptr;
-    if (persistent && nblocks > 0) {
-        const int rs = counter_slot(plan, stream, &c);
-        if (rs) return rs;
-    }
-    std::pair<hipEvent_t, hipEvent_t> ev;
-    int rc = timing_begin(plan, which, stream, &ev);
-    if (rc) return rc;
-    if (persistent && nblocks > 0) {
-        hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(kMaxPieces), 0, stream, c);
-        kp.counter = c;
-        kp.n_items = nblocks;
-        const long resident = (long)plan->n_cu * resident_per_cu<MODE, NW, NP>();
-        nblocks = (int)std::min<long>(nblocks, resident);
-    }
-    rc = persistent ? launch<MODE, NW, NP, true>(kp, nblocks, stream)
-                    : launch<MODE, NW, NP, false>(kp, nblocks, stream);
-    if (rc) return rc;
-    return timing_end(ev, stream);
+    const int64_t items = (int64_t)owners * parts_per_target<MODE, RS>();
+    if (items > INT32_MAX) return fail(OT_FMM_EINVAL, "too many work-list entries");
+    kp.n_items = (int)items;
+    if (!counter) return launch<MODE, RS, false>(kp, (int)items, stream);
+    kp.counter = counter;
+    const int64_t resident = (int64_t)n_cu * resident_per_cu<MODE, RS>();
+    return launch<MODE, RS, true>(kp, (int)std::min<int64_t>(items, resident), stream);
+}
+template <int MODE>
+int launch_any(const KParams& kp, int owners, int* counter, int n_cu, hipStream_t stream)
+{
+    if (owners <= cells_owners<MODE>()) return launch_cells<MODE>(kp, owners, stream);
+    if constexpr (planes_per_wave<MODE>() == 2)
+        return launch_parts<MODE, 4>(kp, owners, counter, n_cu, stream);
+    else
+        return owners < kSplitOwners ? launch_parts<MODE, 4>(kp, owners, counter, n_cu, stream)
+                                     : launch_parts<MODE, 2>(kp, owners, counter, n_cu, stream);
 }
 
 // The work order of a launch: XCD-aware (OT_FMM_SCHED_LOCAL) or longest work
 // first (already in kp.order); a persistent launch in the XCD-aware order
 // takes the pieces with a counter each.
-void apply_order(KParams& kp, const ot_fmm_plan_s* plan, int sched, bool rev)
+void apply_order(KParams& kp, const ot_fmm_plan_s* plan, int sched, bool rev, bool persistent)
 {
     if (!(sched & OT_FMM_SCHED_LOCAL)) return;
-    if ((sched & OT_FMM_SCHED_PERSISTENT) && plan->npieces > 0) {
+    if (persistent && plan->npieces > 0) {
         kp.order = rev ? plan->d_rev_piece : plan->d_fwd_piece;
         kp.npieces = plan->npieces;
         const int* off = rev ? plan->rev_piece_off : plan->fwd_piece_off;
@@ -361,6 +393,25 @@ void apply_order(KParams& kp, const ot_fmm_plan_s* plan, int sched, bool rev)
     } else {
         kp.order = rev ? plan->d_rev_local : plan->d_fwd_local;
     }
+}
+
+// The same with the plan's schedule, timed by its events.
+template <int MODE>
+int launch_timed(ot_fmm_plan plan, int which, KParams kp, int sched, hipStream_t stream)
+{
+    constexpr bool rev = ModeTraits<MODE>::source_role;
+    const int owners = rev ? plan->S : plan->T;
+    int* c = nullptr;
+    if (sched & OT_FMM_SCHED_PERSISTENT) {
+        const int rs = counter_slot(plan, stream, (sched & kOptional) != 0, &c);
+        if (rs) return rs;
+    }
+    apply_order(kp, plan, sched, rev, c != nullptr);
+    std::pair<hipEvent_t, hipEvent_t> ev;
+    int rc = timing_begin(plan, which, stream, &ev);
+    if (rc) return rc;
+    if ((rc = launch_any<MODE>(kp, owners, c, plan->n_cu, stream))) return rc;
+    return timing_end(ev, stream);
 }
 
 int fwd_batched(ot_fmm_plan plan, const double* M, const double* com, double* L, int sched,
@@ -378,20 +429,11 @@ int fwd_batched(ot_fmm_plan plan, const double* M, const double* com, double* L,
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    sched = pick_fwd(sched, plan->tuned_fwd);
-    const bool pers = (sched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(kp, plan, sched, false);
-    const int shape = sched & kShapeMask;
-    if (shape == OT_FMM_SCHED_W8) return launch_timed<MODE_FWD_STORE, 8>(plan, 0, kp, plan->T, pers, stream);
-    if (shape == OT_FMM_SCHED_W16)
-        return launch_timed<MODE_FWD_STORE, 16>(plan, 0, kp, plan->T, pers, stream);
-    if (shape == OT_FMM_SCHED_W8P2)
-        return launch_timed<MODE_FWD_STORE, 8, 2>(plan, 0, kp, plan->T, pers, stream);
-    return fail(OT_FMM_EINVAL, "unknown forward schedule");
+    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, plan->T), stream);
 }
 
 // Forward with the full truncation: the same plan, tables and schedules as
-// the forward (not timed by the plan's events); kFullSched by default.
+// the forward (not timed by the plan's events).
 int fwd_full_batched(ot_fmm_plan plan, const double* M, const double* com, double* L, int sched,
                      hipStream_t stream)
 {
@@ -407,22 +449,12 @@ int fwd_full_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    if (sched == OT_FMM_SCHED_AUTO) sched = kFullSched;
-    const bool pers = (sched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(kp, plan, sched, false);
-    const int shape = sched & kShapeMask;
-    if (shape == OT_FMM_SCHED_W8) return launch_timed<MODE_FULL_STORE, 8>(plan, -1, kp, plan->T, pers, stream);
-    if (shape == OT_FMM_SCHED_W16)
-        return launch_timed<MODE_FULL_STORE, 16>(plan, -1, kp, plan->T, pers, stream);
-    if (shape == OT_FMM_SCHED_W8P2)
-        return launch_timed<MODE_FULL_STORE, 8, 2>(plan, -1, kp, plan->T, pers, stream);
-    return fail(OT_FMM_EINVAL, "unknown forward schedule");
+    return launch_timed<MODE_FULL_STORE>(plan, -1, kp, pick(sched, 0, plan->T), stream);
 }
 
 // Adjoint of the batched forward (FULL: of the full truncation, with
-// derivatives to order 7; kFullSched by default, 16 wavefronts refused -- their
-// register budget is far below what the order-7 sums hold -- and not timed
-// by the plan's events).
+// derivatives to order 7; a target-role shape of 16 wavefronts is refused; not
+// timed by the plan's events).
 template <bool FULL>
 int bwd_any(ot_fmm_plan plan, const double* M, const double* com, const double* gL, double* gM,
             double* gcom, int sched, hipStream_t stream, int passes = 3)
@@ -434,14 +466,10 @@ int bwd_any(ot_fmm_plan plan, const double* M, const double* com, const double* 
     const int w2 = FULL ? -1 : 1, w1 = FULL ? -1 : 2;
     // target-role schedule in the low byte, source-role schedule in the next
     int tsched = sched & 0xff, ssched = (sched >> 8) & 0xff;
-    if (tsched == OT_FMM_SCHED_AUTO)
-        tsched = FULL ? kFullSched
-                      : ((plan->tuned_bwd & 0xff) ? (plan->tuned_bwd & 0xff) : OT_FMM_SCHED_W16);
-    if (ssched == OT_FMM_SCHED_AUTO)
-        ssched = FULL ? kFullSched : ((plan->tuned_bwd >> 8) ? (plan->tuned_bwd >> 8) : kDefaultSourceSched);
-    if (!valid_bwd_sched(tsched | (ssched << 8))) return fail(OT_FMM_EINVAL, "unknown backward schedule");
     if (FULL && (tsched & kShapeMask) == OT_FMM_SCHED_W16)
         return fail(OT_FMM_EINVAL, "16 wavefronts are not available for the full truncation's adjoint");
+    tsched = pick(tsched, FULL ? 0 : plan->tuned_bwd & 0xff, plan->T);
+    ssched = pick(ssched, FULL ? 0 : plan->tuned_bwd >> 8, plan->S);
     const long NS = (long)plan->S * kSub3, NT = (long)plan->T * kSub3;
     // source role: owners are store sub-grids, sources the target cells that see them
     KParams b2{};
@@ -459,14 +487,8 @@ int bwd_any(ot_fmm_plan plan, const double* M, const double* com, const double* 
     b2.out_stride = NS;
     b2.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) b2.period[k] = plan->period[k];
-    // the source-role pass has 8 wavefronts (its 40 accumulators do not fit
-    // the register budget of 16): one pass, or two with split rows
-    const bool spers = (ssched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(b2, plan, ssched, true);
     if (passes & 1) {
-        const int rc = (ssched & kShapeMask) == OT_FMM_SCHED_W8P2
-                           ? launch_timed<kB2, 8, 2>(plan, w2, b2, plan->S, spers, stream)
-                           : launch_timed<kB2, 8>(plan, w2, b2, plan->S, spers, stream);
+        const int rc = launch_timed<kB2>(plan, w2, b2, ssched, stream);
         if (rc) return rc;
     }
     if (!(passes & 2)) return OT_FMM_OK;
@@ -485,13 +507,7 @@ int bwd_any(ot_fmm_plan plan, const double* M, const double* com, const double* 
     b1.out_stride = NS;
     b1.out_blk = plan->d_tgt;
     for (int k = 0; k < 3; ++k) b1.period[k] = plan->period[k];
-    const bool tpers = (tsched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(b1, plan, tsched, false);
-    const int tshape = tsched & kShapeMask;
-    if constexpr (!FULL)
-        if (tshape == OT_FMM_SCHED_W16) return launch_timed<kB1, 16>(plan, w1, b1, plan->T, tpers, stream);
-    if (tshape == OT_FMM_SCHED_W8P2) return launch_timed<kB1, 8, 2>(plan, w1, b1, plan->T, tpers, stream);
-    return launch_timed<kB1, 8>(plan, w1, b1, plan->T, tpers, stream);
+    return launch_timed<kB1>(plan, w1, b1, tsched, stream);
 }
 
 int bwd_batched(ot_fmm_plan plan, const double* M, const double* com, const double* gL, double* gM,
@@ -530,15 +546,7 @@ int fwd_save_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    if (sched == OT_FMM_SCHED_AUTO) sched = (!FULL && plan->tuned_save) ? plan->tuned_save : kSaveSched;
-    const bool pers = (sched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(kp, plan, sched, false);
-    const int shape = sched & kShapeMask;
-    const int which = FULL ? -1 : 3;
-    if (shape == OT_FMM_SCHED_W8) return launch_timed<kMode, 8>(plan, which, kp, plan->T, pers, stream);
-    if (shape == OT_FMM_SCHED_W8P2)
-        return launch_timed<kMode, 8, 2>(plan, which, kp, plan->T, pers, stream);
-    return fail(OT_FMM_EINVAL, "unknown schedule for the forward with saved sums");
+    return launch_timed<kMode>(plan, FULL ? -1 : 3, kp, pick(sched, FULL ? 0 : plan->tuned_save, plan->T), stream);
 }
 
 // Forward with the angular-momentum correction of the force: L, and
@@ -562,14 +570,7 @@ int fwd_amc_batched(ot_fmm_plan plan, const double* M, const double* com, double
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    if (sched == OT_FMM_SCHED_AUTO) sched = plan->tuned_save ? plan->tuned_save : kSaveSched;
-    const bool pers = (sched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(kp, plan, sched, false);
-    const int shape = sched & kShapeMask;
-    if (shape == OT_FMM_SCHED_W8) return launch_timed<MODE_AMC_STORE, 8>(plan, 5, kp, plan->T, pers, stream);
-    if (shape == OT_FMM_SCHED_W8P2)
-        return launch_timed<MODE_AMC_STORE, 8, 2>(plan, 5, kp, plan->T, pers, stream);
-    return fail(OT_FMM_EINVAL, "unknown schedule for the forward with the angular-momentum correction");
+    return launch_timed<MODE_AMC_STORE>(plan, 5, kp, pick(sched, plan->tuned_save, plan->T), stream);
 }
 
 // One-pass adjoint from the saved sums: the source-role pass over every store
@@ -600,16 +601,8 @@ int bwd_saved_batched(ot_fmm_plan plan, const double* M, const double* com, cons
     kp.out_stride = NS;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    if (sched == OT_FMM_SCHED_AUTO)
-        sched = (!FULL && plan->tuned_saved_bwd) ? plan->tuned_saved_bwd : kSaveSched;
-    const bool pers = (sched & OT_FMM_SCHED_PERSISTENT) != 0;
-    apply_order(kp, plan, sched, true);
-    const int shape = sched & kShapeMask;
-    const int which = FULL ? -1 : 4;
-    if (shape == OT_FMM_SCHED_W8) return launch_timed<kMode, 8>(plan, which, kp, plan->S, pers, stream);
-    if (shape == OT_FMM_SCHED_W8P2)
-        return launch_timed<kMode, 8, 2>(plan, which, kp, plan->S, pers, stream);
-    return fail(OT_FMM_EINVAL, "unknown schedule for the one-pass adjoint");
+    return launch_timed<kMode>(plan, FULL ? -1 : 4, kp, pick(sched, FULL ? 0 : plan->tuned_saved_bwd, plan->S),
+                               stream);
 }
 
 int check_plan(ot_fmm_plan plan)
@@ -895,10 +888,10 @@ int capture_step_graph(ot_fmm_plan plan, F&& enqueue)
         plan->capture_log = nullptr;
         plan->capture_stream = nullptr;
     }
-    // slots of a graph that is never instantiated go back to the pool
+    // slots of a graph that is never instantiated go back to their pools
     auto give_back = [&](const std::vector<int>& v) {
         std::lock_guard<std::mutex> lock(plan->slot_mutex);
-        plan->free_capture.insert(plan->free_capture.end(), v.begin(), v.end());
+        for (int slot : v) plan->pool[slot >= kPoolSlots ? 1 : 0].free_capture.push_back(slot);
     };
     e = hipStreamEndCapture(cs, &g);
     (void)hipStreamDestroy(cs);
@@ -1109,7 +1102,7 @@ int ot_fmm_stencil_info(int64_t* slot_pairs, int32_t* offsets_per_target, int32_
     for (int s = 0; s < 27; ++s) slot_pairs[s] = sc.pairs[s];
     for (int pz = 0; pz < 2; ++pz) {
         offsets_per_target[pz] = kStencilHost.count[pz];
-        rows_per_parity[pz] = kStencilHost.range[pz][2 * kReach][2];
+        rows_per_parity[pz] = kStencilHost.range[pz][2 * kReach][1];
     }
     if (!sc.mirror_ok) return fail(OT_FMM_EUNSUPPORTED, "stencil mirror check failed");
     return OT_FMM_OK;
@@ -1538,30 +1531,28 @@ int ot_fmm_autotune_saved(ot_fmm_plan plan, const double* M, const double* com, 
     };
     const int kFlags[4] = {0, OT_FMM_SCHED_PERSISTENT, OT_FMM_SCHED_LOCAL,
                            OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL};
-    int best_f = kSaveSched, best_b = kSaveSched;
+    int best_f = kTunedShape, best_b = kTunedShape;
     float best_fms = 3.0e38f, best_bms = 3.0e38f;
-    for (int shape : {OT_FMM_SCHED_W8, OT_FMM_SCHED_W8P2})
-        for (int f : kFlags) {
-            const int cand = shape | f;
-            float ms = 0.0f;
-            if (!rc) rc = time_it([&] { return fwd_save_batched(plan, M, com, L, Cs, cand, s); }, &ms);
-            if (!rc && ms < best_fms) {
-                best_fms = ms;
-                best_f = cand;
-            }
+    for (int f : kFlags) {
+        const int cand = kTunedShape | f;
+        float ms = 0.0f;
+        if (!rc) rc = time_it([&] { return fwd_save_batched(plan, M, com, L, Cs, cand, s); }, &ms);
+        if (!rc && ms < best_fms) {
+            best_fms = ms;
+            best_f = cand;
         }
+    }
     // the adjoint is timed on the sums of the last forward (any schedule's
     // sums are valid)
-    for (int shape : {OT_FMM_SCHED_W8, OT_FMM_SCHED_W8P2})
-        for (int f : kFlags) {
-            const int cand = shape | f;
-            float ms = 0.0f;
-            if (!rc) rc = time_it([&] { return bwd_saved_batched(plan, M, com, gL, Cs, gM, gcom, cand, s); }, &ms);
-            if (!rc && ms < best_bms) {
-                best_bms = ms;
-                best_b = cand;
-            }
+    for (int f : kFlags) {
+        const int cand = kTunedShape | f;
+        float ms = 0.0f;
+        if (!rc) rc = time_it([&] { return bwd_saved_batched(plan, M, com, gL, Cs, gM, gcom, cand, s); }, &ms);
+        if (!rc && ms < best_bms) {
+            best_bms = ms;
+            best_b = cand;
         }
+    }
     // leave the results of the chosen schedules in the buffers
     if (!rc) rc = fwd_save_batched(plan, M, com, L, Cs, best_f, s);
     if (!rc) rc = bwd_saved_batched(plan, M, com, gL, Cs, gM, gcom, best_b, s);
@@ -1627,12 +1618,12 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
         OT_HIP(hipEventElapsedTime(ms, e0, e1));
         return OT_FMM_OK;
     };
-    // every shape with every combination of the persistent launch and the
-    // XCD-aware order, for each pass on its own: the forward, then the
-    // source-role pass, then the target-role pass
+    // every combination of the persistent launch and the XCD-aware order, for
+    // each pass on its own: the forward, then the source-role pass, then the
+    // target-role pass
     const int kFlags[4] = {0, OT_FMM_SCHED_PERSISTENT, OT_FMM_SCHED_LOCAL,
                            OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL};
-    int best_f = OT_FMM_SCHED_W16;
+    int best_f = kTunedShape;
     float best_ms = 3.0e38f;
     auto try_fwd = [&](int cand) -> int {
         float ms = 0.0f;
@@ -1643,16 +1634,15 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
         }
         return r;
     };
-    for (int shape : {OT_FMM_SCHED_W8, OT_FMM_SCHED_W16, OT_FMM_SCHED_W8P2})
-        for (int f : kFlags)
-            if (!rc) rc = try_fwd(shape | f);
-    int best_b = OT_FMM_SCHED_W16 | (kDefaultSourceSched << 8);
+    for (int f : kFlags)
+        if (!rc) rc = try_fwd(kTunedShape | f);
+    int best_b = OT_FMM_SCHED_BWD(kTunedShape, kTunedShape);
     if (!rc && with_bwd) {
         // source role (bits 8..15), timed alone; then the target role
-        int best_s = kDefaultSourceSched, best_t = OT_FMM_SCHED_W16;
+        int best_s = kTunedShape, best_t = kTunedShape;
         auto try_pass = [&](int passes, int sc, int* best) -> int {
             float ms = 0.0f;
-            const int full = passes == 1 ? (OT_FMM_SCHED_W16 | (sc << 8)) : (sc | (best_s << 8));
+            const int full = passes == 1 ? OT_FMM_SCHED_BWD(kTunedShape, sc) : OT_FMM_SCHED_BWD(sc, best_s);
             int r = time_it([&] { return bwd_any<false>(plan, M, com, gL, gM, gcom, full, s, passes); }, &ms);
             if (!r && ms < best_ms) {
                 best_ms = ms;
@@ -1661,13 +1651,11 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
             return r;
         };
         best_ms = 3.0e38f;
-        for (int shape : {OT_FMM_SCHED_W8, OT_FMM_SCHED_W8P2})
-            for (int f : kFlags)
-                if (!rc) rc = try_pass(1, shape | f, &best_s);
+        for (int f : kFlags)
+            if (!rc) rc = try_pass(1, kTunedShape | f, &best_s);
         best_ms = 3.0e38f;
-        for (int shape : {OT_FMM_SCHED_W8, OT_FMM_SCHED_W16, OT_FMM_SCHED_W8P2})
-            for (int f : kFlags)
-                if (!rc) rc = try_pass(2, shape | f, &best_t);
+        for (int f : kFlags)
+            if (!rc) rc = try_pass(2, kTunedShape | f, &best_t);
         best_b = best_t | (best_s << 8);
         // the target-role trials accumulated into gcom: leave valid results
         if (!rc) rc = bwd_batched(plan, M, com, gL, gM, gcom, best_b, s);
@@ -1909,12 +1897,8 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
     kp.out_stride = NT;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = per[k];
-    kp.counter = head;
-    kp.n_items = T;
     kp.npieces = 0;
-    const long resident = (long)ncu * resident_per_cu<MODE_FWD_STORE, 16, 1>();
-    const int nblocks = (int)std::min<long>(T, resident);
-    if ((rc = launch<MODE_FWD_STORE, 16, 1, true>(kp, nblocks, s))) return rc;
+    if ((rc = launch_any<MODE_FWD_STORE>(kp, T, head, ncu, s))) return rc;
     hipLaunchKernelGGL(k_noalloc_poison, dim3(1024), dim3(256), 0, s, head + 16, L, (long)(20 * NT));
     e = hipGetLastError();
     return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");

@@ -43,7 +43,7 @@ constexpr bool criterion(int ix, int iy, int iz, int jx, int jy, int jz)
 
 struct StencilTable {
     uint32_t rows[2][kMaxRows];           // packed: dy | dx0 << 8 | n << 16
-    int range[2][2 * kReach + 1][3];      // per (pz, dz+9): first row, split row, end row
+    int range[2][2 * kReach + 1][2];      // per (pz, dz+9): first row, end row
     int count[2];                         // offsets per parity (1799)
 };
 
@@ -76,17 +76,8 @@ constexpr StencilTable build_stencil()
                     dx += n;
                 }
             }
-            // split point: first row at which the running count reaches half
-            int split = first, run = 0;
-            while (split < nr && 2 * run < offs) {
-                run += (int)(t.rows[pz][split] >> 16);
-                ++split;
-            }
-            if (split > first && 2 * run - offs > offs - 2 * (run - (int)(t.rows[pz][split - 1] >> 16)))
-                --split;
             t.range[pz][dz + kReach][0] = first;
-            t.range[pz][dz + kReach][1] = split;
-            t.range[pz][dz + kReach][2] = nr;
+            t.range[pz][dz + kReach][1] = nr;
             total += offs;
         }
         t.count[pz] = total;
@@ -129,7 +120,7 @@ SlotCounts compute_slot_counts()
         int n_table = 0;
         for (int dz = -kReach; dz <= kReach; ++dz) {
             const int* rg = kStencilHost.range[pz][dz + kReach];
-            for (int r = rg[0]; r < rg[2]; ++r) {
+            for (int r = rg[0]; r < rg[1]; ++r) {
                 const uint32_t w = kStencilHost.rows[pz][r];
                 const int dy = (int8_t)(w & 0xff), dx0 = (int8_t)((w >> 8) & 0xff), n = (int)(w >> 16);
                 for (int k = 0; k < n; ++k) {
@@ -284,7 +275,7 @@ struct KParams {
     long out_stride;
     const int* out_blk;    // owner -> output block (NULL: identity)
     double period[3];
-    int* counter;          // persistent launch: work counter(s), zeroed before the launch
+    int* counter;          // persistent launch: work counter(s), zero before and after it
     int n_items;           // persistent launch: number of work-list entries
     // persistent launch in pieces (npieces > 0): the work list is cut into
     // npieces consecutive pieces, [piece_off[k], piece_off[k + 1]), one per
@@ -431,227 +422,380 @@ __device__ __forceinline__ void store_sums(const KParams& p, int owner, int cell
     }
 }
 
-// LDS plane layout: cell-major, Layout::stride doubles per cell -- the
-// source record (stage_record of ot_pair.h), then padding. A pair is read with
-// 16-byte loads from one base address (immediate offsets).
-// The cell stride in 16-byte units is odd, so the 8 lanes served per LDS
-// cycle by a 16-byte read -- 8 different cells modulo 8 in the mirrored lane
-// pattern -- fall on disjoint banks.
-template <int MODE>
-struct Layout {
-    static constexpr int nc = ModeTraits<MODE>::nc;
-    static constexpr int nvec = (nc + 1) / 2;                               // 16-byte reads per cell
-    static constexpr int stride = (nvec % 2 == 1) ? 2 * nvec : 2 * nvec + 2;  // doubles per cell
+// ---------------------------------------------------------------------------
+// The source plane in LDS
+// ---------------------------------------------------------------------------
+// The 64 targets of a z-plane reach 448 of the 576 cells of a source plane:
+// the parent criterion cuts half of each corner block away. Rows of 8 to 24
+// cells lie one after the other in LDS, a record of 20 doubles (10 units of
+// 16 bytes) a cell, odd rows at odd units. A 16-byte read serves 16 lanes per
+// cycle, two rows of the mirrored lane pattern: one of even, one of odd y,
+// each with 8 cells that differ modulo 8. The even row's units are even and
+// cover the even bank groups once, the odd row's the odd ones: no conflicts
+// (with records 22 doubles apart and rows packed freely, half of the LDS
+// cycles were conflicts). 70 KiB, so two work-groups fit a CU.
+constexpr int kPlaneCells = 448;
+constexpr int kRecUnits = 10;                             // 16-byte reads of a record
+constexpr int kPlaneUnits = kPlaneCells * kRecUnits + kHalo;
+
+struct PlaneTable {
+    // staging order: the five whole blocks, then the halves of the corner
+    // blocks; unit in LDS | block << 13 | cell of the block's plane << 17 |
+    // squared distance of its parent cell from the targets' parents << 23
+    uint32_t cell[kPlaneCells];
+    int row[kHalo];  // unit of (x, y) in LDS = row[y] + 10 x
+    int cells, units;
 };
 
-template <int MODE, int NW, int NP>
-constexpr int lds_doubles()
+constexpr int parent_gap(int v)
 {
-    constexpr int plane = Layout<MODE>::stride * kPlane;
-    constexpr int merge = (NW == 16 || NP == 2) ? 20 * kSub3 : 0;
-    return plane > merge ? plane : merge;
+    const int q = v / 2;
+    return q < 4 ? 4 - q : (q > 7 ? q - 7 : 0);
 }
 
-// Staging of one source z-plane (the 24 x 24 cells of the 3 x 3 neighbour
-// blocks), one cell per thread: thread v takes cell v & 63 of block v >> 6
-// (the block is wavefront-uniform, so its relation is a scalar load), loads
-// the cell's centre and each of its moments once (a load of a wavefront reads
-// 512 contiguous bytes), forms the source record with
-// compile-time factors, and writes the cell's record with 16-byte LDS
-// stores. A missing neighbour block is staged far away with zero sources.
-template <int MODE, int NW>
-__device__ __forceinline__ void stage_plane(const KParams& p, const int4* rel, int zs, int tid, double* lds)
+constexpr PlaneTable build_plane_table()
+{
+    PlaneTable t{};
+    int at = 0;
+    for (int y = 0; y < kHalo; ++y) {
+        bool first = true;
+        for (int x = 0; x < kHalo; ++x) {
+            if (parent_gap(x) * parent_gap(x) + parent_gap(y) * parent_gap(y) > 16) continue;
+            if (first) {
+                at += (at + y) & 1;
+                t.row[y] = at - kRecUnits * x;
+            }
+            first = false;
+            at += kRecUnits;
+        }
+    }
+    t.units = at;
+    constexpr int order[9] = {4, 1, 3, 5, 7, 0, 2, 6, 8};
+    int n = 0;
+    for (int k = 0; k < 9; ++k)
+        for (int c = 0; c < 64; ++c) {
+            const int x = 8 * (order[k] % 3) + c % 8, y = 8 * (order[k] / 3) + c / 8;
+            const int d2 = parent_gap(x) * parent_gap(x) + parent_gap(y) * parent_gap(y);
+            if (d2 > 16) continue;
+            t.cell[n++] = (uint32_t)(t.row[y] + kRecUnits * x) | (uint32_t)order[k] << 13 | (uint32_t)c << 17 |
+                          (uint32_t)d2 << 23;
+        }
+    t.cells = n;
+    return t;
+}
+constexpr PlaneTable kPlaneTableHost = build_plane_table();
+static_assert(kPlaneTableHost.cells == kPlaneCells && kPlaneTableHost.units <= kPlaneUnits,
+              "cells of a source plane in reach");
+__constant__ PlaneTable c_plane = build_plane_table();
+
+// Rows of the stencil for the two targets of a z-pair (same parent cell, x
+// and y parity 0), per e = source plane - plane of the first: first the
+// offsets of both, then those of the first alone, then of the second alone
+// (the two differ only where the sphere of near cells does).
+struct PairTable {
+    uint32_t rows[kMaxRows];
+    int range[2 * kReach + 1][4];  // per e + kReach
+    int total[3];
+};
+constexpr PairTable build_pair_table()
+{
+    PairTable t{};
+    int nr = 0;
+    for (int e = -kReach; e <= kReach; ++e)
+        for (int which = 0; which < 3; ++which) {
+            t.range[e + kReach][which] = nr;
+            for (int dy = -kReach; dy <= kReach; ++dy)
+                for (int dx = -kReach; dx <= kReach;) {
+                    int n = 0;
+                    for (; dx + n <= kReach; ++n) {
+                        const bool a = criterion(8, 8, 8, 8 + dx + n, 8 + dy, 8 + e);
+                        const bool b = criterion(8, 8, 9, 8 + dx + n, 8 + dy, 8 + e);
+                        if (!(which == 0 ? a && b : which == 1 ? a && !b : b && !a)) break;
+                    }
+                    if (n > 0) {
+                        t.rows[nr++] = pack_row(dy, dx, n);
+                        t.total[which] += n;
+                        dx += n;
+                    } else {
+                        ++dx;
+                    }
+                }
+            t.range[e + kReach][which + 1] = nr;
+        }
+    return t;
+}
+constexpr PairTable kPairTableHost = build_pair_table();
+static_assert(kPairTableHost.total[0] + kPairTableHost.total[1] == 1799 &&
+                  kPairTableHost.total[0] + kPairTableHost.total[2] == 1799,
+              "stencil size");
+static_assert(kPairTableHost.range[2 * kReach][3] + 4 <= kMaxRows &&
+                  kStencilHost.range[0][2 * kReach][1] + 4 <= kMaxRows &&
+                  kStencilHost.range[1][2 * kReach][1] + 4 <= kMaxRows,
+              "a row may be read ahead");
+__constant__ PairTable c_pair = build_pair_table();
+
+// Stages the cells of source plane zs whose parent cell is within `reach2`
+// (squared) of the targets' parents in x and y: a thread takes up to two cells
+// (pk: their table entries), loads the centre and the 20 components (64 lanes
+// read 512 contiguous bytes of a whole block), forms the record and writes it
+// with 16-byte LDS stores. A missing block is staged far away with zero
+// sources: its terms are exact zeros.
+constexpr int kThreads = 256;
+template <int MODE>
+__device__ __forceinline__ void stage_plane(const KParams& p, const int4* s_rel, int zs, int reach2,
+                                            const uint32_t* pk, double2* lds)
 {
     using T = ModeTraits<MODE>;
-    using Lay = Layout<MODE>;
-    for (int v = tid; v < 9 * 64; v += NW * 64) {
-        const int bxy = __builtin_amdgcn_readfirstlane(v >> 6);
-        const int lane = v & 63;
-        const int by = bxy / 3, bx = bxy - 3 * by;
-        const int4 rr = rel[9 * (zs >> 3) + bxy];  // uniform address: scalar load
-        const bool present = rr.x >= 0;
-        const long o = 64 * (zs & 7) + lane;
-        const double* pm = p.mom + (present ? (long)rr.x * kSub3 : 0) + o;
-        const double* px = p.pos + (present ? (long)rr.y * kSub3 : 0) + o;
-        const long sm = p.mom_stride, sx = p.pos_stride;
-        double sh[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) sh[k] = (double)(int)(int8_t)((rr.z >> (8 * k)) & 0xff) * p.period[k];
-        double val[2 * Lay::nvec];
-#pragma unroll
-        for (int c = 0; c < 2 * Lay::nvec; ++c) val[c] = 0.0;
-        if (present) {
+    for (int it = 0; it < 2; ++it) {
+        const int d2 = (int)(pk[it] >> 23);
+        if (d2 > reach2) continue;
+        const int4 rr = s_rel[9 * (zs >> 3) + (int)((pk[it] >> 13) & 15u)];
+        const long o = 64 * (zs & 7) + (int)((pk[it] >> 17) & 63u);
+        double val[2 * kRecUnits];
+        if (rr.x >= 0) {
+            const double* pm = p.mom + (long)rr.x * kSub3 + o;
+            const double* px = p.pos + (long)rr.y * kSub3 + o;
             double raw[20];
 #pragma unroll
-            for (int c = 0; c < 20; ++c) raw[c] = pm[c * sm];
+            for (int c = 0; c < 20; ++c) raw[c] = pm[c * p.mom_stride];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) val[k] = px[k * sx] + sh[k];
+            for (int k = 0; k < 3; ++k)
+                val[k] = px[k * p.pos_stride] + (double)(int)(int8_t)((rr.z >> (8 * k)) & 0xff) * p.period[k];
             stage_record<T::sums, T::source_role>(raw, val);
         } else {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) val[k] = kFar;
+            for (int k = 0; k < 2 * kRecUnits; ++k) val[k] = k < 3 ? kFar : 0.0;
         }
-        double2* dst = reinterpret_cast<double2*>(
-            lds + ((by * 8 + (lane >> 3)) * kHalo + bx * 8 + (lane & 7)) * Lay::stride);
+        double2* dst = lds + (int)(pk[it] & 8191u);
 #pragma unroll
-        for (int j = 0; j < Lay::nvec; ++j) dst[j] = make_double2(val[2 * j], val[2 * j + 1]);
+        for (int j = 0; j < kRecUnits; ++j) dst[j] = make_double2(val[2 * j], val[2 * j + 1]);
     }
 }
 
-// NP = 2 (8 wavefronts): two passes over the source planes, target planes
-// 0-3 then 4-7, two wavefronts per target plane with its stencil rows split
-// in halves as with 16 wavefronts. Each pass stages the 21 source planes in
-// its reach (42 instead of 24), and in exchange the work per staged plane is
-// spread evenly over the 4 SIMDs (about 95% against 86% for one pass with a
-// wavefront per target plane).
-template <int MODE, int NW, int NP, bool PERSIST>
-__global__ void __launch_bounds__(NW * 64) k_interact(const KParams p)
+// Target planes of a wavefront: two where their sums fit the registers (a
+// source record is then read once for both), else one.
+template <int MODE>
+constexpr int planes_per_wave()
+{
+    return ModeTraits<MODE>::nacc <= 16 ? 2 : 1;
+}
+// Work-list entries of a target: 4 wavefronts hold 4 KZ / RS of its 8 planes.
+template <int MODE, int RS>
+constexpr int parts_per_target()
+{
+    return 2 * RS / planes_per_wave<MODE>();
+}
+
+// Batched interaction. A work-group of 4 wavefronts takes a part of a target:
+// RS wavefronts the same KZ target planes (lane = x + 8 y) with the stencil
+// rows dealt in turn, their sums added in order at the end. The source planes
+// in reach of the part are staged one at a time. Two work-groups share a CU,
+// so that one's loads and barriers are hidden by the other's arithmetic.
+//
+// What bounds it: FP64 issue and, above about 80% of it, the power limit (the
+// clock falls from 2.28 GHz at 68% to 2.06 at 88%). Sharing rows instead of
+// planes costs more staging (a part of 2 planes stages 18 source planes) but
+// no wavefront waits for a slower plane at the barriers. 16384 sub-grids, RS =
+// 1 / 2 / 4: forward with saved sums 107.9 / 104.9 / 111.4 ms, full truncation
+// with saved sums 155.6 / 150.9 / 155.1, forward (two planes a wavefront, so
+// a record is read once for both) 57.3 / 53.1 / 52.6, full truncation 113.1 /
+// 102.4 / 99.7; with one plane a wavefront the last two took 57.3 and 106.3
+// (RS = 2, a slower box). One work-group of 8 or 16 wavefronts a target with
+// whole planes of 101 KiB before: forward 55.7, with saved sums 113.5 ms.
+template <int MODE, int RS, bool PERSIST>
+__global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
 {
     using T = ModeTraits<MODE>;
-    using Lay = Layout<MODE>;
-    static_assert(NW == 8 || NW == 16, "8 or 16 wavefronts");
-    static_assert(NP == 1 || (NP == 2 && NW == 8), "two passes: 8 wavefronts");
-    constexpr bool HALVES = NW == 16 || NP == 2;  // two wavefronts per target plane
-    __shared__ double lds[lds_doubles<MODE, NW, NP>()];
+    constexpr int KZ = planes_per_wave<MODE>();
+    constexpr int kParts = parts_per_target<MODE, RS>();
+    constexpr int kPlanes = kSub / kParts;  // target planes of a work-group
+    static_assert(RS == 2 || RS == 4, "wavefronts sharing planes");
+    static_assert(T::nc == 2 * kRecUnits, "record size");
+    static_assert((KZ == 2 ? RS * KZ : (RS - 1) * (4 / RS)) * T::nacc * 64 <= 2 * kPlaneUnits,
+                  "merge through the plane");
+    __shared__ double2 lds2[kPlaneUnits];
+    __shared__ int4 s_rel[27];
+    __shared__ int s_row[kHalo];
+    __shared__ int s_item, s_step;
+    double* lds = reinterpret_cast<double*>(lds2);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = HALVES ? (wave & 1) : 0;
-    // Persistent launch (counter != NULL): the work-group takes work-list
-    // entries from a global counter until the list is exhausted; otherwise it
-    // does the one entry of its index.
-    __shared__ int s_item;
-    constexpr bool persistent = PERSIST;
+    const int sub = wave % RS;  // share of the rows
+    uint32_t pk[2];
+    pk[0] = c_plane.cell[tid];
+    pk[1] = tid + kThreads < kPlaneCells ? c_plane.cell[tid + kThreads] : ~0u;
+    if (tid < kHalo) s_row[tid] = c_plane.row[tid];
+    const int xt = lane & 7, yt = lane >> 3;
+    const int sgx = (xt & 1) ? -1 : 1;
+    const int sgy = (yt & 1) ? -1 : 1;
+    const int step_x = sgx * kRecUnits;
+    // Persistent launch: the work-group takes work-list entries from a counter
+    // until the list is exhausted -- in pieces, from the piece of its XCD
+    // (work-group b runs on XCD b mod npieces), then from the following ones
+    // until every piece is (s_step: pieces left behind) -- else the one of its
+    // index.
     int item = (int)blockIdx.x;
-    // in pieces: the work-group starts on the piece of its XCD (work-group b
-    // runs on XCD b mod npieces) and moves on to the next piece when that is
-    // exhausted, until every piece is (s_step: pieces left behind)
-    __shared__ int s_step;
-    if (persistent && tid == 0) s_step = 0;
+    if (PERSIST && tid == 0) s_step = 0;
 #pragma unroll 1
     for (;;) {
-    if (persistent) {
         __syncthreads();  // the previous entry is finished by every wavefront
-        if (tid == 0) {
-            int it = p.n_items;
-            if (p.npieces > 0) {
-                for (int step = s_step; step < p.npieces; ++step) {
-                    const int k = ((int)blockIdx.x + step) % p.npieces;
+        int index, part;
+        if (PERSIST) {
+            if (tid == 0) {
+                int it = p.n_items;
+                const int np = p.npieces > 0 ? p.npieces : 1;
+                for (int step = s_step; step < np; ++step) {
+                    const int k = ((int)blockIdx.x + step) % np;
+                    const int first = p.npieces > 0 ? kParts * p.piece_off[k] : 0;
+                    const int count = (p.npieces > 0 ? kParts * p.piece_off[k + 1] : p.n_items) - first;
                     const int i = atomicAdd(p.counter + k, 1);
-                    if (i < p.piece_off[k + 1] - p.piece_off[k]) {
-                        it = p.piece_off[k] + i;
+                    if (i < count) {
+                        it = first + i;
                         s_step = step;
                         break;
                     }
+                    // every work-group overruns every counter once: the last
+                    // to do so leaves it zero for the next launch
+                    if (i == count + (int)gridDim.x - 1) atomicExch(p.counter + k, 0);
+                    s_step = step + 1;
                 }
-            } else {
-                it = atomicAdd(p.counter, 1);
+                s_item = it;
             }
-            s_item = it;
+            __syncthreads();
+            item = __builtin_amdgcn_readfirstlane(s_item);
+            if (item >= p.n_items) break;
+            index = item / kParts;  // the parts of a target one after the other: they share their sources
+            part = item % kParts;
+        } else {
+            // a part of every target, then the next: entry i keeps its XCD
+            index = item % (p.n_items / kParts);
+            part = item / (p.n_items / kParts);
         }
-        __syncthreads();
-        item = __builtin_amdgcn_readfirstlane(s_item);
-        if (item >= p.n_items) break;
-    }
-    const int owner = p.order ? p.order[item] : item;
-    const int4* s_rel = p.rel + (long)owner * 27;  // this owner's relations
-#pragma unroll 1
-    for (int pass = 0; pass < NP; ++pass) {
-    // With 8 wavefronts and one pass (wave w on SIMD w % 4) the target planes
-    // are paired per SIMD as (0,4) (1,6) (2,5) (3,7): the pairing whose summed
-    // per-plane work varies least from one staged plane to the next.
-    const int zt = (NW == 16) ? (wave >> 1)
-                 : (NP == 2) ? 4 * pass + (wave >> 1)
-                             : (wave == 5 ? 6 : (wave == 6 ? 5 : wave));
-    const int xt = lane & 7, yt = lane >> 3;
-    const int pz = zt & 1;
-    const int cell = xt + 8 * yt + 64 * zt;
-    const int sgx = (xt & 1) ? -1 : 1;
-    const int sgy = (yt & 1) ? -1 : 1;
-
-    double xi, yi, zi;
-    {
-        const long b = p.own_blk ? p.own_blk[owner] : owner;
-        const long o = b * kSub3 + cell;
-        xi = p.pos[o];
-        yi = p.pos[p.pos_stride + o];
-        zi = p.pos[2 * p.pos_stride + o];
-    }
-
-    double acc[T::nacc];
+        const int owner = p.order ? p.order[index] : index;
+        if (tid < 27) s_rel[tid] = p.rel[(long)owner * 27 + tid];
+        const int z0 = part * kPlanes;                 // first target plane of the work-group
+        const int zt = z0 + KZ * (wave / RS);          // of the wavefront
+        const int cell = xt + 8 * yt + 64 * zt;
+        double xi[KZ], yi[KZ], zi[KZ], acc[KZ * T::nacc];
 #pragma unroll
-    for (int a = 0; a < T::nacc; ++a) acc[a] = 0.0;
+        for (int t = 0; t < KZ; ++t) {
+            const long o = (p.own_blk ? p.own_blk[owner] : owner) * (long)kSub3 + cell + 64 * t;
+            xi[t] = p.pos[o];
+            yi[t] = p.pos[p.pos_stride + o];
+            zi[t] = p.pos[2 * p.pos_stride + o];
+        }
+#pragma unroll
+        for (int a = 0; a < KZ * T::nacc; ++a) acc[a] = 0.0;
 
-    // addresses in 16-byte units of the LDS plane
-    constexpr int cs = Lay::stride / 2;
-    const int lane_off = ((8 + yt) * kHalo + 8 + xt) * cs;
-    const int step_x = sgx * cs;
-    const int step_y = sgy * kHalo * cs;
-    const double2* lds2 = reinterpret_cast<const double2*>(lds);
-
-    const int zs_begin = NP == 2 ? (pass == 0 ? 0 : 8 + 4 - kReach) : 0;
-    const int zs_end = NP == 2 ? (pass == 0 ? 8 + 3 + kReach + 1 : kHalo) : kHalo;
-    for (int zs = zs_begin; zs < zs_end; ++zs) {
-        __syncthreads();
-        stage_plane<MODE, NW>(p, s_rel, zs, tid, lds);
-        __syncthreads();
-        const int dz = zs - (8 + zt);
-        if (dz >= -kReach && dz <= kReach) {
-            const int* rg = c_stencil.range[pz][dz + kReach];
-            int r0 = rg[0], r1 = rg[2];
-            if (HALVES) {
-                if (half == 0)
-                    r1 = rg[1];
-                else
-                    r0 = rg[1];
-            }
-            for (int r = r0; r < r1; ++r) {
-                const uint32_t w = c_stencil.rows[pz][r];
-                const int dy = (int)(int8_t)(w & 0xff);
-                const int dx0 = (int)(int8_t)((w >> 8) & 0xff);
+        // the rows [r0, r1) of a table for the targets T0 .. T1 - 1 of the wavefront
+        auto rows = [&](const uint32_t* table, int r0, int r1, auto t0, auto t1) {
+            int r = r0 + sub;
+            if (r >= r1) return;
+            uint32_t w = table[r];
+            int row = s_row[8 + yt + sgy * (int)(int8_t)(w & 0xff)];
+            for (;;) {
+                // the next row's place is read while this one is worked on
+                const uint32_t wn = table[r + RS];
+                const int next = s_row[8 + yt + sgy * (int)(int8_t)(wn & 0xff)];
+                const double2* src = lds2 + row + kRecUnits * (8 + xt) + step_x * (int)(int8_t)((w >> 8) & 0xff);
                 const int n = (int)(w >> 16);
-                int off = lane_off + dy * step_y + dx0 * step_x;
-                for (int k = 0; k < n; ++k, off += step_x) {
-                    double f[2 * Lay::nvec];
+                for (int k = 0; k < n; ++k, src += step_x) {
+                    double f[2 * kRecUnits];
 #pragma unroll
-                    for (int j = 0; j < Lay::nvec; ++j) {
-                        const double2 v = lds2[off + j];
+                    for (int j = 0; j < kRecUnits; ++j) {
+                        const double2 v = src[j];
                         f[2 * j] = v.x;
                         f[2 * j + 1] = v.y;
                     }
-                    pair_sums<T::sums>(acc, f, xi - f[0], yi - f[1], zi - f[2]);
+#pragma unroll
+                    for (int t = t0; t < t1; ++t)
+                        pair_sums<T::sums>(acc + t * T::nacc, f, xi[t] - f[0], yi[t] - f[1], zi[t] - f[2]);
+                }
+                r += RS;
+                if (r >= r1) break;
+                w = wn;
+                row = next;
+            }
+        };
+
+        const int first = 4 + z0 / 2, last = 4 + (z0 + kPlanes - 1) / 2;  // the targets' parent planes
+        __syncthreads();  // s_rel is there
+        for (int ps = first - 4; ps <= last + 4; ++ps) {
+            // a layer of neighbours that are all missing holds no source
+            if ((ps & 3) == 0 || ps == first - 4) {
+                bool some = false;
+                for (int b = 0; b < 9; ++b) some |= s_rel[9 * (ps >> 2) + b].x >= 0;
+                if (!some) {
+                    ps |= 3;
+                    continue;
+                }
+            }
+            const int gap = ps < first ? first - ps : (ps > last ? ps - last : 0);
+            const int reach2 = 16 - gap * gap;
+#pragma unroll 1
+            for (int zs = 2 * ps; zs < 2 * ps + 2; ++zs) {
+                __syncthreads();  // the previous plane is no longer read
+                stage_plane<MODE>(p, s_rel, zs, reach2, pk, lds2);
+                __syncthreads();
+                const int e = zs - (8 + zt);
+                if (e < -kReach || e > kReach) continue;
+                if constexpr (KZ == 1) {
+                    const int* rg = c_stencil.range[zt & 1][e + kReach];
+                    rows(c_stencil.rows[zt & 1], rg[0], rg[1], std::integral_constant<int, 0>{},
+                         std::integral_constant<int, 1>{});
+                } else {
+                    const int* rg = c_pair.range[e + kReach];
+                    rows(c_pair.rows, rg[0], rg[1], std::integral_constant<int, 0>{},
+                         std::integral_constant<int, KZ>{});
+                    rows(c_pair.rows, rg[1], rg[2], std::integral_constant<int, 0>{},
+                         std::integral_constant<int, 1>{});
+                    rows(c_pair.rows, rg[2], rg[3], std::integral_constant<int, 1>{},
+                         std::integral_constant<int, KZ>{});
                 }
             }
         }
-    }
 
-    // ---------------- epilogues ----------------
-    if constexpr (HALVES) {
-        // the two wavefronts of a target plane add their partial sums, through
-        // LDS in rounds of at most 20 components
+        // the sums of the wavefronts that share planes are added in their order
+        __syncthreads();  // the last plane is no longer read
+        if constexpr (KZ == 2) {
+            // all four share: each of the first two finishes a plane
+            static_assert(RS == 4, "four wavefronts a pair of planes");
 #pragma unroll
-        for (int a0 = 0; a0 < T::nacc; a0 += 20) {
+            for (int a = 0; a < KZ * T::nacc; ++a) lds[(sub * KZ * T::nacc + a) * 64 + lane] = acc[a];
             __syncthreads();
-            if (half == 1) {
+            if (sub < KZ) {
+                const double* from = lds + sub * T::nacc * 64 + lane;
+                double sum[T::nacc];
 #pragma unroll
-                for (int a = a0; a < T::nacc && a < a0 + 20; ++a) lds[(a - a0) * kSub3 + cell] = acc[a];
+                for (int a = 0; a < T::nacc; ++a) {
+                    sum[a] = from[a * 64];
+#pragma unroll
+                    for (int w = 1; w < RS; ++w) sum[a] += from[(w * KZ * T::nacc + a) * 64];
+                }
+                store_sums<MODE>(p, owner, cell + 64 * sub, sum);
+            }
+        } else {
+            double* mine = lds + (wave / RS) * (RS - 1) * T::nacc * 64;
+            if (sub > 0) {
+#pragma unroll
+                for (int a = 0; a < T::nacc; ++a) mine[((sub - 1) * T::nacc + a) * 64 + lane] = acc[a];
             }
             __syncthreads();
-            if (half == 0) {
+            if (sub == 0) {
 #pragma unroll
-                for (int a = a0; a < T::nacc && a < a0 + 20; ++a) acc[a] += lds[(a - a0) * kSub3 + cell];
+                for (int a = 0; a < T::nacc; ++a) {
+#pragma unroll
+                    for (int w = 0; w < RS - 1; ++w) acc[a] += mine[(w * T::nacc + a) * 64 + lane];
+                    if (a % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // few loads in flight: the registers are full
+                }
+                store_sums<MODE>(p, owner, cell, acc);
             }
         }
-        if (half == 1) continue;  // the next pass (none after the last)
+        if (!PERSIST) break;
     }
-    store_sums<MODE>(p, owner, cell, acc);
-    }  // pass
-    if (!persistent) break;
-    }  // work-list entries
 }
-
-// zeroes the kMaxPieces counters of a persistent launch (one per lane)
-__global__ void k_zero_counter(int* c) { c[threadIdx.x] = 0; }
 
 }  // namespace
