@@ -85,12 +85,14 @@ __device__ __forceinline__ int lanes_sum(double* v, int lane, int base, int coun
 // single sub-grid is 256 or 512 work-groups, each thread takes 4 (NT = 512) or
 // 8 sources straight from memory (a source serves both cells of a pair), and
 // the partial sums meet by lane exchange and once through LDS. One sub-grid,
-// forward: 10 us with 512 threads, 12 with 256 (145 with k_interact); with
-// saved sums: 17 and 14 (156). Per sub-grid of many: 11 us with 512 threads, 7
-// with 256, whose sums are merged half as often (k_interact on a full chip: 3.3,
-// since a staged source serves 64 targets there).
+// forward: 8 us with 512 threads, 10 with 256 (145 with k_interact); with
+// saved sums: 14 and 11 (156). Per sub-grid of many: 9 us with 512 threads, 6
+// with 256, whose sums are merged half as often. What bounds it then is the
+// L1: rows of up to 18 cells of 23 components, read once a work-group
+// (k_interact on a full chip takes 3.3 us: a staged source serves 64 or 128
+// targets there).
 template <int MODE, int KT, int NT>
-__global__ void __launch_bounds__(NT) k_cells(const KParams p)
+__global__ void __launch_bounds__(NT, NT == 256 ? 3 : 2) k_cells(const KParams p)
 {
     using T = ModeTraits<MODE>;
     constexpr int kGroups = kSub3 / KT;
@@ -103,8 +105,54 @@ __global__ void __launch_bounds__(NT) k_cells(const KParams p)
     const int g = (int)blockIdx.x % kGroups;
     const int cell0 = KT * g;  // the group's first cell; a pair shares x / 2, y, z
     const int xt = cell0 & 7, yt = (cell0 >> 3) & 7, zt = cell0 >> 6;
+    // halo place hx | hy << 8 | hz << 16 | cells << 24 of a list entry
+    auto place = [&](uint32_t w) {
+        const int dx = (int)(int8_t)(w & 0xff), dy = (int)(int8_t)((w >> 8) & 0xff),
+                  dz = (int)(int8_t)((w >> 16) & 0xff);
+        return (uint32_t)(8 + xt + (KT == 1 && (xt & 1) ? -dx : dx)) |
+               (uint32_t)(8 + yt + ((yt & 1) ? -dy : dy)) << 8 | (uint32_t)(8 + zt + ((zt & 1) ? -dz : dz)) << 16 |
+               (w & 0xff000000u);
+    };
+    // Batched: the entries whose block is there are gathered in list order, so
+    // that no thread is given a missing source (27 targets of an open box,
+    // a third of the sources missing: 164 us with the missing ones skipped in
+    // turn).
+    constexpr int kList = CellSources<KT>::n;
+    __shared__ uint32_t s_list[T::halo ? 1 : kList];
+    int n = kList;
     if constexpr (!T::halo) {
+        __shared__ int s_count[kWaves];
         if (tid < 27) s_rel[tid] = p.rel[(long)owner * 27 + tid];
+        __syncthreads();
+        constexpr int kEach = (kList + NT - 1) / NT;  // consecutive entries of a thread
+        uint32_t mine[kEach];
+        uint32_t there = 0;
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) {
+            const int i = tid * kEach + k;
+            mine[k] = place(c_cell_sources<KT>.at[i < kList ? i : 0]);
+            const int slot = (int)((mine[k] >> 3) & 31u) + 3 * (int)((mine[k] >> 11) & 31u) +
+                             9 * (int)((mine[k] >> 19) & 31u);
+            if (i < kList && s_rel[slot].x >= 0) there |= 1u << k;
+        }
+        // the thread's first entry comes after those of the lanes and wavefronts before it
+        const int had = __popc(there);
+        int at = had;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(at, d);
+            at += (tid & 63) >= d ? v : 0;
+        }
+        if ((tid & 63) == 63) s_count[tid >> 6] = at;
+        at -= had;
+        __syncthreads();
+        n = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            at += w < (tid >> 6) ? s_count[w] : 0;
+            n += s_count[w];
+        }
+#pragma unroll
+        for (int k = 0; k < kEach; ++k)
+            if ((there >> k) & 1u) s_list[at++] = mine[k];
         __syncthreads();
     }
     double xi[KT], yi[KT], zi[KT];
@@ -119,19 +167,19 @@ __global__ void __launch_bounds__(NT) k_cells(const KParams p)
     double acc[kN];
 #pragma unroll
     for (int a = 0; a < kN; ++a) acc[a] = 0.0;
-    for (int i = tid; i < CellSources<KT>::n; i += NT) {
-        const uint32_t w = c_cell_sources<KT>.at[i];
-        const int dx = (int)(int8_t)(w & 0xff), dy = (int)(int8_t)((w >> 8) & 0xff),
-                  dz = (int)(int8_t)((w >> 16) & 0xff);
-        const int hx = 8 + xt + (KT == 1 && (xt & 1) ? -dx : dx), hy = 8 + yt + ((yt & 1) ? -dy : dy),
-                  hz = 8 + zt + ((zt & 1) ? -dz : dz);
+    for (int i = tid; i < n; i += NT) {
+        uint32_t h;
+        if constexpr (T::halo)
+            h = place(c_cell_sources<KT>.at[i]);
+        else
+            h = s_list[i];
+        const int hx = (int)(h & 0xff), hy = (int)((h >> 8) & 0xff), hz = (int)((h >> 16) & 0xff);
         long om, ox;
         double sh[3] = {0.0, 0.0, 0.0};
         if constexpr (T::halo) {
             om = ox = hx + kHalo * hy + kPlane * hz;
         } else {
             const int4 rr = s_rel[(hx >> 3) + 3 * (hy >> 3) + 9 * (hz >> 3)];
-            if (rr.x < 0) continue;  // missing neighbour
             const int c = (hx & 7) + 8 * (hy & 7) + 64 * (hz & 7);
             om = (long)rr.x * kSub3 + c;
             ox = (long)rr.y * kSub3 + c;
@@ -147,7 +195,7 @@ __global__ void __launch_bounds__(NT) k_cells(const KParams p)
         stage_record<T::sums, T::source_role>(raw, rec);
 #pragma unroll
         for (int t = 0; t < KT; ++t)
-            if (KT == 1 || ((w >> (24 + t)) & 1u))
+            if (KT == 1 || ((h >> (24 + t)) & 1u))
                 pair_sums<T::sums>(acc + t * T::nacc, rec, xi[t] - rec[0], yi[t] - rec[1], zi[t] - rec[2]);
     }
     const int mine = lanes_sum<kN, 32>(acc, tid & 63, 0, kN);

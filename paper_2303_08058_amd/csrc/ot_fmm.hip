@@ -102,26 +102,30 @@ int ensure_device()
 namespace {
 
 
-template <int MODE, int RS, bool PERSIST>
+template <int MODE, int KZ, int RS, bool PERSIST>
 int launch(const KParams& kp, int nblocks, hipStream_t stream)
 {
     if (nblocks <= 0) return OT_FMM_OK;
-    hipLaunchKernelGGL((k_interact<MODE, RS, PERSIST>), dim3(nblocks), dim3(kThreads), 0, stream, kp);
+    hipLaunchKernelGGL((k_interact<MODE, KZ, RS, PERSIST>), dim3(nblocks), dim3(kThreads), 0, stream, kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return OT_FMM_OK;
 }
 
 // The target cells of `owners` owners by k_cells: 512 threads for the pairs of
-// cells of a single sub-grid (256 work-groups), else 256.
+// cells of a single sub-grid (256 work-groups), else 256. A multipole block
+// takes as long with either (13.6 us), but work-groups of 256 let blocks on
+// several streams share the CUs (64 on 16 streams: 730 us with 512, 610 with
+// 256, 680 with 128).
 template <int MODE>
 int launch_cells(const KParams& kp, int owners, hipStream_t stream)
 {
     constexpr int kt = cells_per_group<MODE>();
     const dim3 grid((unsigned)owners * (kSub3 / kt));
-    if (kt == 2 && owners == 1)
-        hipLaunchKernelGGL((k_cells<MODE, kt, kt == 2 ? 512 : 256>), grid, dim3(512), 0, stream, kp);
-    else if constexpr (!ModeTraits<MODE>::halo)
+    constexpr bool kWide = kt == 2 && MODE != MODE_FWD_HALO;
+    if (kWide && owners == 1)
+        hipLaunchKernelGGL((k_cells<MODE, kt, kWide ? 512 : 256>), grid, dim3(512), 0, stream, kp);
+    else if constexpr (MODE != MODE_MONO_HALO)
         hipLaunchKernelGGL((k_cells<MODE, kt, 256>), grid, dim3(256), 0, stream, kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
@@ -129,20 +133,20 @@ int launch_cells(const KParams& kp, int owners, hipStream_t stream)
 }
 
 // Up to this many targets (or store sub-grids) k_cells is faster than the
-// work-groups of k_interact, which do not fill the chip: forward of 27 (open
-// box) 191 us against 243, of 48 354 against 249; with saved sums 16 142
-// against 167, 27 374 against 260.
+// work-groups of k_interact, which do not fill the chip: forward 98 us against
+// 151 for 18 targets, 203 against 155 for 27; with saved sums 202 against 253
+// and about 300 against 260.
 template <int MODE>
 constexpr int cells_owners()
 {
-    return cells_per_group<MODE>() == 2 ? 32 : 18;
+    return cells_per_group<MODE>() == 2 ? 24 : 20;
 }
 
-// Below this many targets (or store sub-grids), modes with a plane a wavefront
-// let four wavefronts share one (8 work-groups a target) instead of two.
-// Forward with saved sums of 27 targets: 294 us against 474 with two; 64: 494
-// against 496; 693: 4.89 against 4.58 ms.
-constexpr int kSplitOwners = 64;
+// Up to this many targets (or store sub-grids) four wavefronts share each
+// target plane: 8 work-groups a target, against 4 of two planes. Forward of 27
+// / 64 / 80 / 100 targets 155 / 253 / 374 / 475 us against 243 / 253 / 411 /
+// 420, with saved sums 260 / 462 / 666 / 870 against 461 / 481 / 810 / 828.
+constexpr int kSplitOwners = 84;
 
 // Every shape selects the same kernel; the tuners try the flags on this one.
 constexpr int kTunedShape = OT_FMM_SCHED_W8;
@@ -298,12 +302,12 @@ int timing_end(const std::pair<hipEvent_t, hipEvent_t>& ev, hipStream_t stream)
 
 // Work-groups of one instantiation resident per CU (LDS and registers), from
 // the runtime's occupancy calculator, computed once.
-template <int MODE, int RS>
+template <int MODE, int KZ, int RS>
 int resident_per_cu()
 {
     static const int n = [] {
         int b = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, RS, true>, kThreads, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, KZ, RS, true>, kThreads, 0) != hipSuccess ||
             b < 1)
             b = 1;
         return b;
@@ -357,26 +361,26 @@ int counter_slot(ot_fmm_plan plan, hipStream_t stream, bool optional, int** out)
 // One launch of k_interact over all parts of `owners` targets (or store
 // sub-grids): a work-group per entry, or (counter given) as many work-groups as
 // fit the device at once, taking entries from it.
-template <int MODE, int RS>
+template <int MODE, int KZ, int RS>
 int launch_parts(KParams kp, int owners, int* counter, int n_cu, hipStream_t stream)
 {
-    const int64_t items = (int64_t)owners * parts_per_target<MODE, RS>();
+    const int64_t items = (int64_t)owners * parts_per_target(KZ, RS);
     if (items > INT32_MAX) return fail(OT_FMM_EINVAL, "too many work-list entries");
     kp.n_items = (int)items;
-    if (!counter) return launch<MODE, RS, false>(kp, (int)items, stream);
+    if (!counter) return launch<MODE, KZ, RS, false>(kp, (int)items, stream);
     kp.counter = counter;
-    const int64_t resident = (int64_t)n_cu * resident_per_cu<MODE, RS>();
-    return launch<MODE, RS, true>(kp, (int)std::min<int64_t>(items, resident), stream);
+    const int64_t resident = (int64_t)n_cu * resident_per_cu<MODE, KZ, RS>();
+    return launch<MODE, KZ, RS, true>(kp, (int)std::min<int64_t>(items, resident), stream);
 }
 template <int MODE>
 int launch_any(const KParams& kp, int owners, int* counter, int n_cu, hipStream_t stream)
 {
     if (owners <= cells_owners<MODE>()) return launch_cells<MODE>(kp, owners, stream);
+    if (owners <= kSplitOwners) return launch_parts<MODE, 1, 4>(kp, owners, counter, n_cu, stream);
     if constexpr (planes_per_wave<MODE>() == 2)
-        return launch_parts<MODE, 4>(kp, owners, counter, n_cu, stream);
+        return launch_parts<MODE, 2, 4>(kp, owners, counter, n_cu, stream);
     else
-        return owners < kSplitOwners ? launch_parts<MODE, 4>(kp, owners, counter, n_cu, stream)
-                                     : launch_parts<MODE, 2>(kp, owners, counter, n_cu, stream);
+        return launch_parts<MODE, 1, 2>(kp, owners, counter, n_cu, stream);
 }
 
 // The work order of a launch: XCD-aware (OT_FMM_SCHED_LOCAL) or longest work

@@ -581,11 +581,7 @@ constexpr int planes_per_wave()
     return ModeTraits<MODE>::nacc <= 16 ? 2 : 1;
 }
 // Work-list entries of a target: 4 wavefronts hold 4 KZ / RS of its 8 planes.
-template <int MODE, int RS>
-constexpr int parts_per_target()
-{
-    return 2 * RS / planes_per_wave<MODE>();
-}
+constexpr int parts_per_target(int kz, int rs) { return 2 * rs / kz; }
 
 // Batched interaction. A work-group of 4 wavefronts takes a part of a target:
 // RS wavefronts the same KZ target planes (lane = x + 8 y) with the stencil
@@ -603,12 +599,11 @@ constexpr int parts_per_target()
 // 102.4 / 99.7; with one plane a wavefront the last two took 57.3 and 106.3
 // (RS = 2, a slower box). One work-group of 8 or 16 wavefronts a target with
 // whole planes of 101 KiB before: forward 55.7, with saved sums 113.5 ms.
-template <int MODE, int RS, bool PERSIST>
+template <int MODE, int KZ, int RS, bool PERSIST>
 __global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
 {
     using T = ModeTraits<MODE>;
-    constexpr int KZ = planes_per_wave<MODE>();
-    constexpr int kParts = parts_per_target<MODE, RS>();
+    constexpr int kParts = parts_per_target(KZ, RS);
     constexpr int kPlanes = kSub / kParts;  // target planes of a work-group
     static_assert(RS == 2 || RS == 4, "wavefronts sharing planes");
     static_assert(T::nc == 2 * kRecUnits, "record size");
