@@ -89,6 +89,28 @@ struct TreeParams {
     int Sp;
 };
 
+// A pass that moves much more than the 256 MiB memory-side cache holds (NT)
+// reads its cell arrays once and finds nothing of them there, so it loads and
+// stores them past the caches: at 32768 child nodes M2M 655 -> 630 us, L2L
+// 1158 -> 1050, evaluation 1094 -> 996 (5.5 to 5.9 TB/s; a plain device copy
+// reaches 4.7, a sum 6.1), at 4096 84 -> 69, 152 -> 125 and 163 -> 142. Below,
+// the passes before have left part of them there: 1728 nodes (300 MB), all
+// three 185 us against 195 past the caches.
+constexpr int64_t kStreamBytes = (int64_t)400 << 20;
+
+template <bool NT>
+__device__ __forceinline__ double load(const double* p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool NT>
+__device__ __forceinline__ void store(double v, double* p)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // Cross-lane exchange inside a wavefront through DPP (no LDS traffic): the
 // value held by lane ^ 1 (quad permutation [1, 0, 3, 2]) or by lane ^ 8
 // (rotation by 8 inside each row of 16 lanes).
@@ -120,6 +142,7 @@ __device__ __forceinline__ double quad_sum(double v)
 // wavefronts of the work-group assemble one full 8x8 parent plane that is
 // stored as 512-byte rows (directly from the lanes, the stores were 32-byte
 // pieces and the pass 20% slower).
+template <bool NT>
 __global__ void __launch_bounds__(256) k_m2m(const TreeParams p)
 {
     // work-group = one z-plane of a parent node (8 per node): its 4 wavefronts
@@ -144,8 +167,8 @@ __global__ void __launch_bounds__(256) k_m2m(const TreeParams p)
     }
 #pragma unroll
     for (int b = 0; b < 20; ++b) {
-        m0[b] = p.m_in[b * nc + j0];
-        m1[b] = p.m_in[b * nc + j1];
+        m0[b] = load<NT>(p.m_in + b * nc + j0);
+        m1[b] = load<NT>(p.m_in + b * nc + j1);
     }
     const double m = quad_sum(m0[0] + m1[0]);
 #pragma unroll
@@ -220,6 +243,7 @@ __device__ __forceinline__ void l2l_shift(double* out, const double* lp, const d
 // Downward pass: one thread per child cell (the child node of parent `node`
 // at octant o, cell c); each child node has one parent, so writes never race.
 // (Read per thread from global memory, the parent values took 5% longer.)
+template <bool NT>
 __global__ void __launch_bounds__(256) k_l2l(const TreeParams p)
 {
     // work-group = 4 child z-planes (256 cells) of one child node; its 32
@@ -246,12 +270,12 @@ __global__ void __launch_bounds__(256) k_l2l(const TreeParams p)
 #pragma unroll
     for (int a = 0; a < 20; ++a) lp[a] = s_lp[a][r];
 #pragma unroll
-    for (int a = 0; a < 20; ++a) out[a] = p.m_out[a * p.n_child + j];
+    for (int a = 0; a < 20; ++a) out[a] = load<NT>(p.m_out + a * p.n_child + j);
     monomials(p.x_in2[j] - s_lp[20][r], p.x_in2[p.n_child + j] - s_lp[21][r],
               p.x_in2[2 * p.n_child + j] - s_lp[22][r], mono);
     l2l_shift(out, lp, mono, std::make_integer_sequence<int, 20>{});
 #pragma unroll
-    for (int a = 0; a < 20; ++a) p.m_out[a * p.n_child + j] = out[a];
+    for (int a = 0; a < 20; ++a) store<NT>(out[a], p.m_out + a * p.n_child + j);
 }
 
 // F_k = - sum_{|a| <= 2} M_a / a! L_{a+e_k},  W = 1/2 sum_{|a| <= 3} M_a / a! L_a
@@ -274,6 +298,7 @@ __device__ __forceinline__ void eval_all(const double* m, const double* l, doubl
     (eval_term<A>(m, l, f, w), ...);
 }
 
+template <bool NT>
 __global__ void __launch_bounds__(256) k_evaluate(const double* M, const double* L, double* F,
                                                   double* W, long n)
 {
@@ -282,14 +307,14 @@ __global__ void __launch_bounds__(256) k_evaluate(const double* M, const double*
     double m[20], l[20], f[3] = {0.0, 0.0, 0.0}, w = 0.0;
 #pragma unroll
     for (int a = 0; a < 20; ++a) {
-        m[a] = M[a * n + i];
-        l[a] = L[a * n + i];
+        m[a] = load<NT>(M + a * n + i);
+        l[a] = load<NT>(L + a * n + i);
     }
     eval_all(m, l, f, w, std::make_integer_sequence<int, 20>{});
-    F[i] = f[0];
-    F[n + i] = f[1];
-    F[2 * n + i] = f[2];
-    W[i] = 0.5 * w;
+    store<NT>(f[0], F + i);
+    store<NT>(f[1], F + n + i);
+    store<NT>(f[2], F + 2 * n + i);
+    store<NT>(0.5 * w, W + i);
 }
 
 }  // namespace
@@ -383,7 +408,9 @@ int ot_fmm_m2m(ot_fmm_tree tree, const double* Mc, const double* comc, double* M
     tp.n_parent = (long)tree->Sp * kSub3;
     tp.Sp = tree->Sp;
     // 8 work-groups of 4 wavefronts per parent node
-    hipLaunchKernelGGL(k_m2m, dim3((unsigned)tree->Sp * 8), dim3(256), 0, (hipStream_t)stream, tp);
+    const bool nt = (int64_t)tree->Sp * 9 * kSub3 * 23 * 8 > kStreamBytes;
+    hipLaunchKernelGGL(nt ? k_m2m<true> : k_m2m<false>, dim3((unsigned)tree->Sp * 8), dim3(256), 0,
+                       (hipStream_t)stream, tp);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");
 }
@@ -413,7 +440,9 @@ int ot_fmm_l2l(ot_fmm_tree tree, const double* Lp, const double* comp, const dou
     tp.Sp = tree->Sp;
     const long n = (long)tree->Sp * 8 * kSub3;
     // 16 work-groups of 256 child cells per parent node
-    hipLaunchKernelGGL(k_l2l, dim3((unsigned)(n / 256)), dim3(256), 0, (hipStream_t)stream, tp);
+    const bool nt = (int64_t)n * 43 * 8 > kStreamBytes;
+    hipLaunchKernelGGL(nt ? k_l2l<true> : k_l2l<false>, dim3((unsigned)(n / 256)), dim3(256), 0, (hipStream_t)stream,
+                       tp);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");
 }
@@ -430,7 +459,8 @@ int ot_fmm_evaluate(int64_t ncells, const double* M, const double* L, double* F,
         return fail(OT_FMM_EINVAL, "outputs overlap inputs or each other");
     int rc = ensure_device();
     if (rc) return rc;
-    hipLaunchKernelGGL(k_evaluate, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0,
+    const bool nt = ncells * 44 * 8 > kStreamBytes;
+    hipLaunchKernelGGL(nt ? k_evaluate<true> : k_evaluate<false>, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0,
                        (hipStream_t)stream, M, L, F, W, (long)ncells);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");

@@ -353,3 +353,50 @@ def test_momentum_balance_closed_domain(ot, n):
         rF, rW = oracle.evaluate(M, oracle.batched_forward(batch, M, X))
         assert np.allclose(f, rF, rtol=0, atol=1e-11 * np.abs(rF).max())
         assert np.allclose(w, rW, rtol=0, atol=1e-11 * np.abs(rW).max())
+
+
+@pytest.mark.parametrize("n", [(400 << 20) // (44 * 8), (400 << 20) // (44 * 8) + 1])
+def test_evaluation_agrees_on_both_sides_of_the_cache_size(ot, n):
+    """The evaluation of n cells, just below and just above the size from which
+    it bypasses the caches, equals that of the same cells in short pieces bit
+    for bit (the last piece ends in a partial work-group)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    M = torch.randn((20, n), dtype=torch.float64, device="cuda", generator=gen)
+    L = torch.randn((20, n), dtype=torch.float64, device="cuda", generator=gen)
+    F, W = torch.empty((3, n), dtype=torch.float64, device="cuda"), torch.empty(n, dtype=torch.float64, device="cuda")
+    ot.ot_fmm_evaluate(M, L, F, W)
+    for a, b in ((0, 1000), (n // 2, n // 2 + 300000), (n - 777, n)):
+        Fp = torch.empty((3, b - a), dtype=torch.float64, device="cuda")
+        Wp = torch.empty(b - a, dtype=torch.float64, device="cuda")
+        ot.ot_fmm_evaluate(M[:, a:b].contiguous(), L[:, a:b].contiguous(), Fp, Wp)
+        assert torch.equal(F[:, a:b], Fp) and torch.equal(W[a:b], Wp)
+
+
+def test_tree_passes_agree_on_both_sides_of_the_cache_size(ot):
+    """M2M and L2L of 4096 child nodes (past the caches) equal the same nodes'
+    of trees of 8 children, bit for bit."""
+    import torch
+    n = 16
+    ch = synthetic.octree_children(n)
+    S, Sp = n ** 3, ch.shape[0]
+    M, X = synthetic.device_lattice_store(n, 5)
+    f64 = dict(dtype=torch.float64, device="cuda")
+    Mp, Xp = torch.empty((20, Sp * 512), **f64), torch.empty((3, Sp * 512), **f64)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    L0 = torch.randn((20, S * 512), generator=gen, **f64)
+    Lp = torch.randn((20, Sp * 512), generator=gen, **f64)
+    tree = ot.Tree(ch, S)
+    tree.m2m(M, X, Mp, Xp)
+    L = L0.clone()
+    tree.l2l(Lp, Xp, X, L)
+    one = ot.Tree(np.arange(8, dtype=np.int32)[None], 8)
+    for p in (0, 100, Sp - 1):
+        cols = torch.from_numpy((ch[p].astype(np.int64)[:, None] * 512 + np.arange(512)).reshape(-1)).cuda()
+        mine = slice(512 * p, 512 * (p + 1))
+        Mq, Xq = torch.empty((20, 512), **f64), torch.empty((3, 512), **f64)
+        one.m2m(M[:, cols].contiguous(), X[:, cols].contiguous(), Mq, Xq)
+        assert torch.equal(Mp[:, mine], Mq) and torch.equal(Xp[:, mine], Xq)
+        Lq = L0[:, cols].contiguous()
+        one.l2l(Lp[:, mine].contiguous(), Xp[:, mine].contiguous(), X[:, cols].contiguous(), Lq)
+        assert torch.equal(L[:, cols], Lq)
