@@ -1763,10 +1763,11 @@ static __device__ __align__(256) int4 scratch[kScrInt4];
 std::mutex g_scratch_mutex;
 int4* g_scratch_ptr[kNoAllocDevices];  // per device, set once
 int g_scratch_ncu[kNoAllocDevices];
+int g_scratch_nxcd[kNoAllocDevices];
 
-// This device's copy of `scratch` and its CU count, looked up on the first
-// call on the device (with the device current) and kept.
-int scratch_of_current_device(int4** base, int* ncu)
+// This device's copy of `scratch` and its CU and XCD counts, looked up on the
+// first call on the device (with the device current) and kept.
+int scratch_of_current_device(int4** base, int* ncu, int* nxcd)
 {
     int dev = 0;
     OT_HIP(hipGetDevice(&dev));
@@ -1780,33 +1781,41 @@ int scratch_of_current_device(int4** base, int* ncu)
         int n = 0;
         OT_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
         g_scratch_ncu[dev] = n > 0 ? n : 1;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess || n < 1) n = 1;
+        g_scratch_nxcd[dev] = n;
         g_scratch_ptr[dev] = static_cast<int4*>(ptr);
     }
     *base = g_scratch_ptr[dev];
     *ncu = g_scratch_ncu[dev];
+    *nxcd = g_scratch_nxcd[dev];
     return OT_FMM_OK;
 }
 
 // Clears the header: the work counters and the invalid-entry count start at
 // zero, the first invalid entry at INT_MAX (a kernel, so that graph captures
 // hold no memset node).
-__global__ void k_noalloc_reset(int* head)
+__device__ __forceinline__ void noalloc_reset(int* head, int t)
 {
-    const int t = threadIdx.x;
-    if (t < 16) head[t] = 0;
-    if (t == 16) head[16] = 0;
+    if (t < 17) head[t] = 0;
     if (t == 17) head[17] = 0x7fffffff;
 }
+__global__ void k_noalloc_reset(int* head) { noalloc_reset(head, threadIdx.x); }
 
 // Relation table of the call from the caller's device descriptor, checked
 // entry by entry: an entry out of range is dropped (stored as missing, its
-// target's own block as 0) and counted.
-__global__ void __launch_bounds__(256) k_noalloc_relations(int S, int T, const int* __restrict__ tgt,
-                                                           const int* __restrict__ nbr,
-                                                           const int8_t* __restrict__ shift, int* own,
-                                                           int4* rel, int* status)
+// target's own block as 0) and counted; the forward then writes NaN. A single
+// work-group (up to 37 targets) clears the header itself: one launch less.
+__global__ void __launch_bounds__(1024) k_noalloc_relations(int S, int T, const int* __restrict__ tgt,
+                                                            const int* __restrict__ nbr,
+                                                            const int8_t* __restrict__ shift, int* own,
+                                                            int4* rel, int* head)
 {
-    const int i = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    if (gridDim.x == 1) {
+        noalloc_reset(head, threadIdx.x);
+        __syncthreads();
+    }
+    int* status = head + 16;
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (i >= T * 27) return;
     const int t = i / 27, s = i - 27 * t;
     const int ob = tgt[t];
@@ -1823,14 +1832,6 @@ __global__ void __launch_bounds__(256) k_noalloc_relations(int S, int T, const i
     }
     rel[i] = make_int4(b, b, packed, 0);
     if (s == 13) own[t] = own_ok ? ob : 0;
-}
-
-// After a call with invalid entries every element of L becomes NaN.
-__global__ void __launch_bounds__(256) k_noalloc_poison(const int* status, double* L, long n)
-{
-    if (status[0] == 0) return;
-    const double nan = __builtin_nan("");
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) L[i] = nan;
 }
 
 // Do the byte ranges [a, a + na) and [b, b + nb) share memory?
@@ -1876,19 +1877,23 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
     int rc = ensure_device();
     if (rc) return rc;
     int4* base = nullptr;
-    int ncu = 1;
-    if ((rc = scratch_of_current_device(&base, &ncu))) return rc;
+    int ncu = 1, nxcd = 1;
+    if ((rc = scratch_of_current_device(&base, &ncu, &nxcd))) return rc;
     int* head = reinterpret_cast<int*>(base);
     int* own = reinterpret_cast<int*>(base + kScrHead);
     int4* rel = base + kScrHead + kScrOwn;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_noalloc_reset, dim3(1), dim3(64), 0, s, head);
-    hipLaunchKernelGGL(k_noalloc_relations, dim3((unsigned)((T * 27 + 255) / 256)), dim3(256), 0, s, (int)S,
-                       (int)T, tgt, nbr, shift, own, rel, head + 16);
+    const int entries = (int)T * 27;
+    const bool one = entries <= 1024;
+    if (!one) hipLaunchKernelGGL(k_noalloc_reset, dim3(1), dim3(64), 0, s, head);
+    hipLaunchKernelGGL(k_noalloc_relations, dim3(one ? 1 : (unsigned)((entries + 255) / 256)), dim3(one ? 1024 : 256), 0,
+                       s, (int)S, (int)T, tgt, nbr, shift, own, rel, head);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
-    // the forward of ot_fmm_multipole_batched with W16 | PERSISTENT, work
-    // entries in target order from the scratch counter
+    // the forward of ot_fmm_multipole_batched, persistent, work entries in
+    // target order from the scratch counters: with as many targets as AUTO asks
+    // for, a piece of the targets per XCD, so that the work-groups of an XCD
+    // share sources where neighbouring targets follow each other
     KParams kp{};
     kp.mom = M;
     kp.pos = com;
@@ -1901,11 +1906,12 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
     kp.out_stride = NT;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = per[k];
-    kp.npieces = 0;
-    if ((rc = launch_any<MODE_FWD_STORE>(kp, T, head, ncu, s))) return rc;
-    hipLaunchKernelGGL(k_noalloc_poison, dim3(1024), dim3(256), 0, s, head + 16, L, (long)(20 * NT));
-    e = hipGetLastError();
-    return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");
+    if (T >= kPersistentOwners && nxcd <= kMaxPieces) {
+        kp.npieces = nxcd;
+        for (int k = 0; k <= nxcd; ++k) kp.piece_off[k] = (int)((int64_t)T * k / nxcd);
+    }
+    kp.invalid = head + 16;  // any: every element of L becomes NaN
+    return launch_any<MODE_FWD_STORE>(kp, T, head, ncu, s);
 }
 
 int ot_fmm_noalloc_status(int32_t* invalid, int32_t* first_invalid)
@@ -1915,8 +1921,8 @@ int ot_fmm_noalloc_status(int32_t* invalid, int32_t* first_invalid)
     int rc = ensure_device();
     if (rc) return rc;
     int4* base = nullptr;
-    int ncu = 1;
-    if ((rc = scratch_of_current_device(&base, &ncu))) return rc;
+    int ncu = 1, nxcd = 1;
+    if ((rc = scratch_of_current_device(&base, &ncu, &nxcd))) return rc;
     OT_HIP(hipDeviceSynchronize());
     int st[2] = {0, 0};
     OT_HIP(hipMemcpy(st, reinterpret_cast<int*>(base) + 16, sizeof(st), hipMemcpyDeviceToHost));

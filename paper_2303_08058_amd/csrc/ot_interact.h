@@ -274,6 +274,7 @@ struct KParams {
     double* out1;          // gX (B2), the saved target-role sums (FS) or the force correction (AMC)
     long out_stride;
     const int* out_blk;    // owner -> output block (NULL: identity)
+    const int* invalid;    // forward: a count that, if not zero, makes the outputs NaN (NULL: none)
     double period[3];
     int* counter;          // persistent launch: work counter(s), zero before and after it
     int n_items;           // persistent launch: number of work-list entries
@@ -363,6 +364,12 @@ __device__ __forceinline__ void store_sums(const KParams& p, int owner, int cell
     } else if constexpr (!T::adjoint) {
         double L[20];
         expand<0>(acc, L, std::make_integer_sequence<int, 20>{});
+        if constexpr (MODE == MODE_FWD_STORE) {
+            if (p.invalid && *p.invalid != 0) {
+#pragma unroll
+                for (int a = 0; a < 20; ++a) L[a] = __builtin_nan("");
+            }
+        }
         const long b = p.out_blk ? p.out_blk[owner] : owner;
 #pragma unroll
         for (int a = 0; a < 20; ++a) p.out0[a * p.out_stride + b * kSub3 + cell] = L[a];

@@ -125,3 +125,38 @@ def test_invalid_entry_is_dropped_reported_and_poisons_L(ot):
     good = _noalloc(ot, batch, M, X)
     assert ot.ot_fmm_noalloc_status()[0] == 0
     assert np.array_equal(good, _with_plan(ot, batch, M, X))
+
+
+@pytest.mark.parametrize("n", [1, 37, 38, 64])
+def test_descriptor_checks_at_every_size(ot, n):
+    """Up to 37 targets one work-group clears the status and checks the table,
+    beyond a kernel before it: an invalid entry makes every output NaN either
+    way, and the next call is clean."""
+    rng = synthetic._rng(45)
+    M, X = synthetic.store_field(4, rng, 2.0, 3.0, 0.6, sep=6.0)
+    full = synthetic.lattice_batch(4)
+    batch = {"S": 64, "T": n, "tgt": full["tgt"][:n], "nbr": full["nbr"][:n].copy(), "shift": full["shift"][:n],
+             "period": full["period"]}
+    bad = dict(batch, nbr=batch["nbr"].copy())
+    bad["nbr"][n - 1, 26] = -2
+    bad["nbr"][n // 2, 3] = 64
+    got = _noalloc(ot, bad, M, X)
+    assert ot.ot_fmm_noalloc_status() == (2, 27 * (n // 2) + 3)
+    assert np.isnan(got).all()
+    good = _noalloc(ot, batch, M, X)
+    assert ot.ot_fmm_noalloc_status()[0] == 0
+    assert np.array_equal(good, _with_plan(ot, batch, M, X))
+
+
+def test_pieces_per_xcd_change_nothing(ot):
+    """729 targets (work entries in a piece per XCD): bitwise the plan's."""
+    import torch
+    b = synthetic.apply_missing(synthetic.lattice_batch(9), 0.2, synthetic._rng(46))
+    M, X = synthetic.device_lattice_store(9, 46)
+    dev = {k: torch.from_numpy(np.ascontiguousarray(b[k])).cuda() for k in ("tgt", "nbr", "shift")}
+    L = torch.full((20, 729 * 512), float("nan"), dtype=torch.float64, device="cuda")
+    R = torch.full_like(L, float("nan"))
+    for rep in range(2):
+        ot.ot_fmm_multipole_batched_noalloc(729, 729, dev["tgt"], dev["nbr"], dev["shift"], b["period"], M, X, L)
+    ot.Plan.from_batch(b).multipole_batched(M, X, R, sched=1)
+    assert torch.equal(L, R)
