@@ -170,25 +170,32 @@ def version() -> int:
     return _lib.ot_fmm_version()
 
 
+# Handle of a device's current stream without the torch.cuda.Stream object that
+# torch.cuda.current_stream() makes for each question.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
+        return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
-def _dptr(t, shape, name):
+def _dptr(t, shape, name, Tensor=torch.Tensor, float64=torch.float64):
     """Device pointer of a contiguous float64 GPU tensor of the given shape."""
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, Tensor):
         raise TypeError("%s must be a torch tensor" % name)
-    if t.device.type != "cuda" or t.dtype != torch.float64 or not t.is_contiguous():
+    if not t.is_cuda or t.dtype is not float64 or not t.is_contiguous():
         raise ValueError("%s must be a contiguous float64 GPU tensor" % name)
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # ---------------------------------------------------------------------------
