@@ -52,10 +52,14 @@ struct CoarseShape {
 // With 8 wavefronts (a whole target) the accumulators go through LDS at the
 // end so that L is read and written in cell order; smaller work-groups add
 // into their cells directly. FULL: the full truncation (every |b| <= 3 for
-// every |a| <= 3), with the same kept outputs as the total order; its pair step
-// needs about 150 registers, so it runs at half the waves per SIMD.
-template <int NW, bool FULL>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(FULL ? 2 : 4)))
+// every |a| <= 3), with the same kept outputs as the total order. Its pair step
+// takes about 150 registers; held to 128 (WAVES = 4 per SIMD, two work-groups
+// a CU, 13 of them spilled) it is faster as soon as every CU has two
+// work-groups: 6554 targets 1.20 ms against 1.72, 819 217 us against 227, 102
+// 150 against 144. The pass is bound by the latency of a pair's chain (mask
+// bit, LDS gather, derivatives), so what counts is the wavefronts in flight.
+template <int NW, bool FULL, int WAVES>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WAVES)))
 k_coarse_fine(const CoarseParams p)
 {
     using Sh = CoarseShape<NW>;

@@ -1275,10 +1275,12 @@ static int coarse_fine_any(bool full, ot_fmm_plan plan, const double* com, const
     cp.out_stride = NT;
     for (int k = 0; k < 3; ++k) cp.period[k] = plan->period[k];
     const dim3 grid((unsigned)plan->n_coarse_items), block(kCoarseWaves * 64);
-    if (full)
-        hipLaunchKernelGGL((k_coarse_fine<kCoarseWaves, true>), grid, block, 0, (hipStream_t)stream, cp);
+    if (!full)
+        hipLaunchKernelGGL((k_coarse_fine<kCoarseWaves, false, 4>), grid, block, 0, (hipStream_t)stream, cp);
+    else if (plan->n_coarse_items >= 2 * plan->n_cu)
+        hipLaunchKernelGGL((k_coarse_fine<kCoarseWaves, true, 4>), grid, block, 0, (hipStream_t)stream, cp);
     else
-        hipLaunchKernelGGL((k_coarse_fine<kCoarseWaves, false>), grid, block, 0, (hipStream_t)stream, cp);
+        hipLaunchKernelGGL((k_coarse_fine<kCoarseWaves, true, 2>), grid, block, 0, (hipStream_t)stream, cp);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? OT_FMM_OK : hip_fail(e, "kernel launch");
 }
