@@ -56,11 +56,44 @@ constexpr int cells_per_group()
     return ModeTraits<MODE>::nacc <= 16 ? 2 : 1;
 }
 
+// v of the lane whose number differs in BIT (8), or in BIT and all lower bits
+// (4, 2, 1): one DPP move.
+template <int BIT>
+__device__ __forceinline__ double lane_pair(double v)
+{
+    constexpr int kCtrl = BIT == 8 ? 0x128 : BIT == 4 ? 0x141 : BIT == 2 ? 0x1b : 0xb1;
+    int2 w = __builtin_bit_cast(int2, v);
+    w.x = __builtin_amdgcn_mov_dpp(w.x, kCtrl, 0xf, 0xf, true);
+    w.y = __builtin_amdgcn_mov_dpp(w.y, kCtrl, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, w);
+}
+
+// Exchanges a's upper with b's lower half of every 2 BIT lanes (BIT 32, 16).
+template <int BIT>
+__device__ __forceinline__ void swap_halves(double& a, double& b)
+{
+    const uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    uint2 u, w;
+    if constexpr (BIT == 32) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false);
+        u = make_uint2(lo[0], hi[0]);
+        w = make_uint2(lo[1], hi[1]);
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+        u = make_uint2(lo[0], hi[0]);
+        w = make_uint2(lo[1], hi[1]);
+    }
+    a = __builtin_bit_cast(double, u);
+    b = __builtin_bit_cast(double, w);
+}
+
 // Adds v[0 .. N) over the 64 lanes of a wavefront: each step hands half of
-// the values to the lane across one bit of the lane number and keeps the
-// other half, so N values cost about N exchanges instead of 6 N. Returns the
-// index whose sum this lane ends up with, in v[0], or -1. The order of the
-// additions is fixed.
+// the values to a lane whose number differs in BIT and keeps the other half,
+// so N values cost about N exchanges instead of 6 N. Returns the index whose
+// sum this lane ends up with, in v[0], or -1. The order of the additions is
+// fixed.
 template <int N, int BIT>
 __device__ __forceinline__ int lanes_sum(double* v, int lane, int base, int count)
 {
@@ -71,8 +104,13 @@ __device__ __forceinline__ int lanes_sum(double* v, int lane, int base, int coun
         const bool up = (lane & BIT) != 0;
 #pragma unroll
         for (int i = 0; i < H; ++i) {
-            const double lo = v[i], hi = i + H < N ? v[i + H] : 0.0;
-            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, BIT);
+            double lo = v[i], hi = i + H < N ? v[i + H] : 0.0;
+            if constexpr (BIT >= 16) {
+                swap_halves<BIT>(lo, hi);
+                v[i] = lo + hi;
+            } else {
+                v[i] = (up ? hi : lo) + lane_pair<BIT>(up ? lo : hi);
+            }
         }
         base += up ? H : 0;
         count = up ? count - H : (count < H ? count : H);
@@ -82,17 +120,19 @@ __device__ __forceinline__ int lanes_sum(double* v, int lane, int base, int coun
 
 // One work-group of NT threads per KT target cells. A launch over few targets
 // leaves most of the chip idle when a work-group owns a plane of cells; here a
-// single sub-grid is 256 or 512 work-groups, each thread takes 4 (NT = 512) or
-// 8 sources straight from memory (a source serves both cells of a pair), and
-// the partial sums meet by lane exchange and once through LDS. One sub-grid,
-// forward: 8 us with 512 threads, 10 with 256 (145 with k_interact); with
-// saved sums: 14 and 11 (156). Per sub-grid of many: 9 us with 512 threads, 6
-// with 256, whose sums are merged half as often. What bounds it then is the
-// L1: rows of up to 18 cells of 23 components, read once a work-group
-// (k_interact on a full chip takes 3.3 us: a staged source serves 64 or 128
-// targets there).
+// single sub-grid is 256 or 512 work-groups, each thread takes a few sources
+// (4 of NT = 512) straight from memory (a source serves both cells of a pair),
+// and the partial sums meet by lane exchange and once through LDS. Work-groups
+// go to the XCDs in turn: each takes one z-plane of cells of every target, so
+// that an L2 holds the 11 to 19 source planes in reach instead of all (64
+// blocks on 16 streams 771 -> 726 us, with the exchange through registers). One
+// sub-grid, forward: 8 us (145 with k_interact); with saved sums 11 (156); of
+// 18, 4.7 and 9.3 each. What bounds it then is the L1 (rows of up to 18 cells
+// of 23 components, read once a work-group) and the list and the merge, about
+// half of the instructions (k_interact on a full chip takes 3.1 us: a staged
+// source serves 64 or 128 targets there).
 template <int MODE, int KT, int NT>
-__global__ void __launch_bounds__(NT, NT == 256 ? 3 : 2) k_cells(const KParams p)
+__global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_cells(const KParams p)
 {
     using T = ModeTraits<MODE>;
     constexpr int kGroups = kSub3 / KT;
@@ -102,7 +142,7 @@ __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 2) k_cells(const KParams p
     __shared__ int4 s_rel[27];
     const int tid = threadIdx.x;
     const int owner = (int)blockIdx.x / kGroups;
-    const int g = (int)blockIdx.x % kGroups;
+    const int g = (int)(blockIdx.x & 7u) * (kGroups / 8) + (((int)blockIdx.x % kGroups) >> 3);
     const int cell0 = KT * g;  // the group's first cell; a pair shares x / 2, y, z
     const int xt = cell0 & 7, yt = (cell0 >> 3) & 7, zt = cell0 >> 6;
     // halo place hx | hy << 8 | hz << 16 | cells << 24 of a list entry

@@ -106,47 +106,47 @@ template <int MODE, int KZ, int RS, bool PERSIST>
 int launch(const KParams& kp, int nblocks, hipStream_t stream)
 {
     if (nblocks <= 0) return OT_FMM_OK;
-    hipLaunchKernelGGL((k_interact<MODE, KZ, RS, PERSIST>), dim3(nblocks), dim3(kThreads), 0, stream, kp);
+    hipLaunchKernelGGL((k_interact<MODE, KZ, RS, PERSIST>), dim3(nblocks), dim3(64 * group_waves(RS)), 0, stream, kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return OT_FMM_OK;
 }
 
 // The target cells of `owners` owners by k_cells: 512 threads for the pairs of
-// cells of a single sub-grid (256 work-groups), else 256. A multipole block
-// takes as long with either (13.6 us), but work-groups of 256 let blocks on
-// several streams share the CUs (64 on 16 streams: 730 us with 512, 610 with
-// 256, 680 with 128).
+// cells of a single sub-grid (256 work-groups), 256 for its multipole block
+// (a block takes as long with either, 13.6 us, but work-groups of 256 let
+// blocks on several streams share the CUs: 64 on 16 streams 730 us with 512,
+// 610 with 256, 680 with 128), else 128, whose sums are merged least often (8
+// sub-grids forward 42 us with 256, 40 with 128, 42 with 64; with saved sums
+// 79, 71 and 79).
 template <int MODE>
 int launch_cells(const KParams& kp, int owners, hipStream_t stream)
 {
     constexpr int kt = cells_per_group<MODE>();
     const dim3 grid((unsigned)owners * (kSub3 / kt));
-    constexpr bool kWide = kt == 2 && MODE != MODE_FWD_HALO;
-    if (kWide && owners == 1)
-        hipLaunchKernelGGL((k_cells<MODE, kt, kWide ? 512 : 256>), grid, dim3(512), 0, stream, kp);
-    else if constexpr (MODE != MODE_MONO_HALO)
-        hipLaunchKernelGGL((k_cells<MODE, kt, 256>), grid, dim3(256), 0, stream, kp);
+    constexpr bool kHaloPairs = MODE == MODE_FWD_HALO;
+    constexpr int kFew = kt == 2 && !kHaloPairs ? 512 : kHaloPairs ? 256 : 128;
+    if (owners == 1)
+        hipLaunchKernelGGL((k_cells<MODE, kt, kFew>), grid, dim3(kFew), 0, stream, kp);
+    else if constexpr (!ModeTraits<MODE>::halo)
+        hipLaunchKernelGGL((k_cells<MODE, kt, 128>), grid, dim3(128), 0, stream, kp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return OT_FMM_OK;
 }
 
-// Up to this many targets (or store sub-grids) k_cells is faster than the
-// work-groups of k_interact, which do not fill the chip: forward 98 us against
-// 151 for 18 targets, 203 against 155 for 27; with saved sums 202 against 253
-// and about 300 against 260.
-template <int MODE>
-constexpr int cells_owners()
-{
-    return cells_per_group<MODE>() == 2 ? 24 : 20;
-}
+// Up to this many targets (or store sub-grids) k_cells takes no longer than the
+// work-groups of k_interact, whose time does not fall below that of one target:
+// forward of 18 targets of an open box 84 us against 112, with saved sums 168
+// against 198, of 27 with every neighbour 184 and 378 against 116 and 205 (k_cells'
+// time goes with the pairs, which the host does not know for tables on the device).
+constexpr int kCellOwners = 20;
 
-// Up to this many targets (or store sub-grids) four wavefronts share each
-// target plane: 8 work-groups a target, against 4 of two planes. Forward of 27
-// / 64 / 80 / 100 targets 155 / 253 / 374 / 475 us against 243 / 253 / 411 /
-// 420, with saved sums 260 / 462 / 666 / 870 against 461 / 481 / 810 / 828.
-constexpr int kSplitOwners = 84;
+// Up to this many work-groups of 8 wavefronts a CU they are ahead of those of
+// 4: forward of 32 / 64 / 80 / 100 targets 114 / 241 / 356 / 474 us against (two
+// planes a wavefront) 243 / 253 / 411 / 400, with saved sums 205 / 431 / 639 / 860
+// against 461 / 481 / 810 / 804.
+constexpr int kWideRounds = 3;
 
 // Every shape selects the same kernel; the tuners try the flags on this one.
 constexpr int kTunedShape = OT_FMM_SCHED_W8;
@@ -307,7 +307,8 @@ int resident_per_cu()
 {
     static const int n = [] {
         int b = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, KZ, RS, true>, kThreads, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_interact<MODE, KZ, RS, true>,
+                                                         64 * group_waves(RS), 0) != hipSuccess ||
             b < 1)
             b = 1;
         return b;
@@ -367,16 +368,21 @@ int launch_parts(KParams kp, int owners, int* counter, int n_cu, hipStream_t str
     const int64_t items = (int64_t)owners * parts_per_target(KZ, RS);
     if (items > INT32_MAX) return fail(OT_FMM_EINVAL, "too many work-list entries");
     kp.n_items = (int)items;
-    if (!counter) return launch<MODE, KZ, RS, false>(kp, (int)items, stream);
-    kp.counter = counter;
-    const int64_t resident = (int64_t)n_cu * resident_per_cu<MODE, KZ, RS>();
-    return launch<MODE, KZ, RS, true>(kp, (int)std::min<int64_t>(items, resident), stream);
+    if constexpr (RS != 8) {
+        if (counter) {
+            kp.counter = counter;
+            const int64_t resident = (int64_t)n_cu * resident_per_cu<MODE, KZ, RS>();
+            return launch<MODE, KZ, RS, true>(kp, (int)std::min<int64_t>(items, resident), stream);
+        }
+    }
+    return launch<MODE, KZ, RS, false>(kp, (int)items, stream);
 }
 template <int MODE>
 int launch_any(const KParams& kp, int owners, int* counter, int n_cu, hipStream_t stream)
 {
-    if (owners <= cells_owners<MODE>()) return launch_cells<MODE>(kp, owners, stream);
-    if (owners <= kSplitOwners) return launch_parts<MODE, 1, 4>(kp, owners, counter, n_cu, stream);
+    if (owners <= kCellOwners) return launch_cells<MODE>(kp, owners, stream);
+    if (owners * (int64_t)kSub <= (int64_t)kWideRounds * n_cu)
+        return launch_parts<MODE, 1, 8>(kp, owners, nullptr, n_cu, stream);  // too few entries to deal out
     if constexpr (planes_per_wave<MODE>() == 2)
         return launch_parts<MODE, 2, 4>(kp, owners, counter, n_cu, stream);
     else

@@ -87,7 +87,6 @@ constexpr StencilTable build_stencil()
 
 constexpr StencilTable kStencilHost = build_stencil();
 static_assert(kStencilHost.count[0] == 1799 && kStencilHost.count[1] == 1799, "stencil size");
-__constant__ StencilTable c_stencil = build_stencil();
 
 // Exact number of pairs between the 8^3 target cells and the neighbour block
 // at each slot, plus a check that the mirrored table reproduces the stencil
@@ -535,49 +534,134 @@ constexpr PairTable kPairTableHost = build_pair_table();
 static_assert(kPairTableHost.total[0] + kPairTableHost.total[1] == 1799 &&
                   kPairTableHost.total[0] + kPairTableHost.total[2] == 1799,
               "stencil size");
-static_assert(kPairTableHost.range[2 * kReach][3] + 4 <= kMaxRows &&
-                  kStencilHost.range[0][2 * kReach][1] + 4 <= kMaxRows &&
-                  kStencilHost.range[1][2 * kReach][1] + 4 <= kMaxRows,
-              "a row may be read ahead");
-__constant__ PairTable c_pair = build_pair_table();
 
-// Stages the cells of source plane zs whose parent cell is within `reach2`
-// (squared) of the targets' parents in x and y: a thread takes up to two cells
-// (pk: their table entries), loads the centre and the 20 components (64 lanes
-// read 512 contiguous bytes of a whole block), forms the record and writes it
-// with 16-byte LDS stores. A missing block is staged far away with zero
-// sources: its terms are exact zeros.
-constexpr int kThreads = 256;
+// The rows of a plane dealt to the RS wavefronts that share it, which wait for
+// each other at the plane's barrier: the longest row left goes to the
+// wavefront with the least so far (a row also costs about a quarter of a
+// cell); four and more wavefronts take rows of more than 9 cells in pieces.
+// Dealt in turn, the busiest wavefronts took 1.14 (RS = 2), 1.20 (RS = 4, pairs
+// of targets) and 1.53 (RS = 8) times the mean, summed over the planes; so
+// 1.09, 1.07 and 1.20. 4096 sub-grids: forward 13.05 -> 12.52 ms, full
+// truncation 24.7 -> 23.6, with saved sums 25.9 -> 25.5; 32 sub-grids (RS = 8)
+// 122 -> 114 us.
+// KZ = 1: one list a wavefront, for either z parity; KZ = 2: PairTable's three.
+template <int KZ, int RS>
+struct RowShares {
+    static constexpr int kTables = KZ == 1 ? 2 : 1, kLists = KZ == 1 ? 1 : 3;
+    uint32_t rows[kTables][kMaxRows];
+    int range[kTables][2 * kReach + 1][RS][kLists + 1];
+    int cells[kTables][kLists];
+};
+template <int KZ, int RS>
+constexpr RowShares<KZ, RS> build_row_shares()
+{
+    using R = RowShares<KZ, RS>;
+    R t{};
+    for (int z = 0; z < R::kTables; ++z) {
+        int nr = 0;
+        for (int e = 0; e <= 2 * kReach; ++e) {
+            uint32_t piece[128] = {};
+            int list[128] = {}, cost[128] = {}, owner[128] = {}, n = 0;
+            for (int l = 0; l < R::kLists; ++l) {
+                const int r0 = KZ == 1 ? kStencilHost.range[z][e][0] : kPairTableHost.range[e][l];
+                const int r1 = KZ == 1 ? kStencilHost.range[z][e][1] : kPairTableHost.range[e][l + 1];
+                for (int r = r0; r < r1; ++r) {
+                    const uint32_t w = KZ == 1 ? kStencilHost.rows[z][r] : kPairTableHost.rows[r];
+                    const int dy = (int)(w << 24) >> 24, dx = (int)(w << 16) >> 24, len = (int)(w >> 16);
+                    const int cuts = RS == 2 ? 1 : (len + 8) / 9;
+                    for (int k = 0; k < cuts; ++k) {
+                        const int from = len * k / cuts, to = len * (k + 1) / cuts;
+                        piece[n] = pack_row(dy, dx + from, to - from);
+                        list[n] = l;
+                        cost[n] = 4 * (to - from) * (KZ == 2 && l == 0 ? 2 : 1) + 1;
+                        owner[n++] = -1;
+                        t.cells[z][l] += to - from;
+                    }
+                }
+            }
+            int load[RS] = {};
+            for (int done = 0; done < n; ++done) {
+                int best = -1, least = 0;
+                for (int i = 0; i < n; ++i)
+                    if (owner[i] < 0 && (best < 0 || cost[i] > cost[best])) best = i;
+                for (int w = 1; w < RS; ++w)
+                    if (load[w] < load[least]) least = w;
+                owner[best] = least;
+                load[least] += cost[best];
+            }
+            for (int w = 0; w < RS; ++w)
+                for (int l = 0; l <= R::kLists; ++l) {
+                    t.range[z][e][w][l] = nr;
+                    for (int i = 0; l < R::kLists && i < n; ++i)
+                        if (owner[i] == w && list[i] == l) t.rows[z][nr++] = piece[i];
+                }
+        }
+    }
+    return t;
+}
+template <int KZ, int RS>
+struct RowSharesOf {
+    static constexpr RowShares<KZ, RS> host = build_row_shares<KZ, RS>();
+    static_assert(KZ == 1 ? host.cells[0][0] == 1799 && host.cells[RowShares<KZ, RS>::kTables - 1][0] == 1799
+                          : host.cells[0][0] == kPairTableHost.total[0] &&
+                                host.cells[0][RowShares<KZ, RS>::kLists - 2] == kPairTableHost.total[1] &&
+                                host.cells[0][RowShares<KZ, RS>::kLists - 1] == kPairTableHost.total[2],
+                  "every cell dealt once");
+    static_assert(host.range[RowShares<KZ, RS>::kTables - 1][2 * kReach][RS - 1][RowShares<KZ, RS>::kLists] + 1 <=
+                      kMaxRows,
+                  "a row may be read ahead");
+};
+template <int KZ, int RS>
+__constant__ RowShares<KZ, RS> c_shares = RowSharesOf<KZ, RS>::host;
+
+// A cell of a source plane on its way into LDS: load_cell takes the centre and
+// the 20 components from memory (64 lanes read 512 contiguous bytes of a whole
+// block) if the cell's parent is within `reach2` (squared) of the targets'
+// parents in x and y; put_cell forms the record and writes it with 16-byte LDS
+// stores. A missing block is staged far away with zero sources: its terms are
+// exact zeros. pk: the cell's table entry.
+struct StagedCell {
+    double raw[20], x[3];
+    int shift;
+    bool in, there;
+};
 template <int MODE>
-__device__ __forceinline__ void stage_plane(const KParams& p, const int4* s_rel, int zs, int reach2,
-                                            const uint32_t* pk, double2* lds)
+__device__ __forceinline__ void load_cell(const KParams& p, const int4* s_rel, int zs, int reach2, uint32_t pk,
+                                          StagedCell& s)
+{
+    s.in = (int)(pk >> 23) <= reach2;
+    s.there = false;
+    if (!s.in) return;
+    const int4 rr = s_rel[9 * (zs >> 3) + (int)((pk >> 13) & 15u)];
+    if (rr.x < 0) return;
+    s.there = true;
+    s.shift = rr.z;
+    const long o = 64 * (zs & 7) + (int)((pk >> 17) & 63u);
+    const double* pm = p.mom + (long)rr.x * kSub3 + o;
+    const double* px = p.pos + (long)rr.y * kSub3 + o;
+#pragma unroll
+    for (int c = 0; c < 20; ++c) s.raw[c] = pm[c * p.mom_stride];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s.x[k] = px[k * p.pos_stride];
+}
+template <int MODE>
+__device__ __forceinline__ void put_cell(const KParams& p, const StagedCell& s, uint32_t pk, double2* lds)
 {
     using T = ModeTraits<MODE>;
+    if (!s.in) return;
+    double val[2 * kRecUnits];
+    if (s.there) {
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const int d2 = (int)(pk[it] >> 23);
-        if (d2 > reach2) continue;
-        const int4 rr = s_rel[9 * (zs >> 3) + (int)((pk[it] >> 13) & 15u)];
-        const long o = 64 * (zs & 7) + (int)((pk[it] >> 17) & 63u);
-        double val[2 * kRecUnits];
-        if (rr.x >= 0) {
-            const double* pm = p.mom + (long)rr.x * kSub3 + o;
-            const double* px = p.pos + (long)rr.y * kSub3 + o;
-            double raw[20];
+        for (int k = 0; k < 3; ++k)
+            val[k] = s.x[k] + (double)(int)(int8_t)((s.shift >> (8 * k)) & 0xff) * p.period[k];
+        stage_record<T::sums, T::source_role>(s.raw, val);
+    } else {
 #pragma unroll
-            for (int c = 0; c < 20; ++c) raw[c] = pm[c * p.mom_stride];
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                val[k] = px[k * p.pos_stride] + (double)(int)(int8_t)((rr.z >> (8 * k)) & 0xff) * p.period[k];
-            stage_record<T::sums, T::source_role>(raw, val);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 2 * kRecUnits; ++k) val[k] = k < 3 ? kFar : 0.0;
-        }
-        double2* dst = lds + (int)(pk[it] & 8191u);
-#pragma unroll
-        for (int j = 0; j < kRecUnits; ++j) dst[j] = make_double2(val[2 * j], val[2 * j + 1]);
+        for (int k = 0; k < 2 * kRecUnits; ++k) val[k] = k < 3 ? kFar : 0.0;
     }
+    double2* dst = lds + (int)(pk & 8191u);
+#pragma unroll
+    for (int j = 0; j < kRecUnits; ++j) dst[j] = make_double2(val[2 * j], val[2 * j + 1]);
 }
 
 // Target planes of a wavefront: two where their sums fit the registers (a
@@ -587,36 +671,50 @@ constexpr int planes_per_wave()
 {
     return ModeTraits<MODE>::nacc <= 16 ? 2 : 1;
 }
-// Work-list entries of a target: 4 wavefronts hold 4 KZ / RS of its 8 planes.
-constexpr int parts_per_target(int kz, int rs) { return 2 * rs / kz; }
+// Wavefronts of a work-group, and the work-list entries of a target: they hold
+// KZ planes for each RS wavefronts.
+constexpr int group_waves(int rs) { return rs == 8 ? 8 : 4; }
+constexpr int parts_per_target(int kz, int rs) { return kSub * rs / (group_waves(rs) * kz); }
 
-// Batched interaction. A work-group of 4 wavefronts takes a part of a target:
-// RS wavefronts the same KZ target planes (lane = x + 8 y) with the stencil
-// rows dealt in turn, their sums added in order at the end. The source planes
-// in reach of the part are staged one at a time. Two work-groups share a CU,
-// so that one's loads and barriers are hidden by the other's arithmetic.
+// Batched interaction. A work-group takes a part of a target: RS wavefronts
+// (lane = x + 8 y) share the same KZ target planes, the stencil rows dealt to
+// them, their sums added in order at the end. The source planes in reach of
+// the part are staged in LDS one at a time.
 //
-// What bounds it: FP64 issue and, above about 80% of it, the power limit (the
-// clock falls from 2.28 GHz at 68% to 2.06 at 88%). Sharing rows instead of
-// planes costs more staging (a part of 2 planes stages 18 source planes) but
-// no wavefront waits for a slower plane at the barriers. 16384 sub-grids, RS =
+// RS = 2 and 4: work-groups of 4 wavefronts, two on a CU, so that one's loads
+// and barriers are hidden by the other's arithmetic. What bounds it: FP64 issue
+// and, above about 80% of it, the power limit (the clock falls from 2.28 GHz at
+// 68% to 2.06 at 88%). Sharing rows instead of planes costs more staging (a
+// part of 2 planes stages 18 source planes) but no wavefront waits for a
+// slower plane at the barriers. 16384 sub-grids with rows dealt in turn, RS =
 // 1 / 2 / 4: forward with saved sums 107.9 / 104.9 / 111.4 ms, full truncation
 // with saved sums 155.6 / 150.9 / 155.1, forward (two planes a wavefront, so
 // a record is read once for both) 57.3 / 53.1 / 52.6, full truncation 113.1 /
 // 102.4 / 99.7; with one plane a wavefront the last two took 57.3 and 106.3
 // (RS = 2, a slower box). One work-group of 8 or 16 wavefronts a target with
 // whole planes of 101 KiB before: forward 55.7, with saved sums 113.5 ms.
+//
+// RS = 8: one work-group of 8 wavefronts a CU on one target plane, for launches
+// that would leave CUs empty or with one work-group. Nothing else hides its
+// loads, so two planes are in LDS (141 KiB) and the next one's components come
+// into registers while one is worked on: one barrier a plane. 27 targets of an
+// open box: 116 us, of it 92 FP64 issue (155 with 4 wavefronts and one plane);
+// with saved sums 205 (260). A full chip is better served by two work-groups:
+// 4096 sub-grids 15.5 ms against 12.5, with saved sums 28.9 against 26.3.
 template <int MODE, int KZ, int RS, bool PERSIST>
-__global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
+__global__ void __launch_bounds__(64 * group_waves(RS), 2) k_interact(const KParams p)
 {
     using T = ModeTraits<MODE>;
+    constexpr int kThreads = 64 * group_waves(RS);
+    constexpr bool kAhead = RS == 8;  // two planes in LDS, the next one's loads in flight
     constexpr int kParts = parts_per_target(KZ, RS);
     constexpr int kPlanes = kSub / kParts;  // target planes of a work-group
-    static_assert(RS == 2 || RS == 4, "wavefronts sharing planes");
+    static_assert(RS == 2 || RS == 4 || (RS == 8 && KZ == 1), "wavefronts sharing planes");
     static_assert(T::nc == 2 * kRecUnits, "record size");
-    static_assert((KZ == 2 ? RS * KZ : (RS - 1) * (4 / RS)) * T::nacc * 64 <= 2 * kPlaneUnits,
+    static_assert((KZ == 2 ? RS * KZ : (RS - 1) * (group_waves(RS) / RS)) * T::nacc * 64 <=
+                      (kAhead ? 4 : 2) * kPlaneUnits,
                   "merge through the plane");
-    __shared__ double2 lds2[kPlaneUnits];
+    __shared__ double2 lds2[(kAhead ? 2 : 1) * kPlaneUnits];
     __shared__ int4 s_rel[27];
     __shared__ int s_row[kHalo];
     __shared__ int s_item, s_step;
@@ -626,8 +724,8 @@ __global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = wave % RS;  // share of the rows
-    uint32_t pk[2];
-    pk[0] = c_plane.cell[tid];
+    uint32_t pk[2];  // the thread's cells of a plane
+    pk[0] = tid < kPlaneCells ? c_plane.cell[tid] : ~0u;
     pk[1] = tid + kThreads < kPlaneCells ? c_plane.cell[tid + kThreads] : ~0u;
     if (tid < kHalo) s_row[tid] = c_plane.row[tid];
     const int xt = lane & 7, yt = lane >> 3;
@@ -693,16 +791,15 @@ __global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
         for (int a = 0; a < KZ * T::nacc; ++a) acc[a] = 0.0;
 
         // the rows [r0, r1) of a table for the targets T0 .. T1 - 1 of the wavefront
-        auto rows = [&](const uint32_t* table, int r0, int r1, auto t0, auto t1) {
-            int r = r0 + sub;
-            if (r >= r1) return;
-            uint32_t w = table[r];
+        auto rows = [&](const double2* plane, const uint32_t* table, int r0, int r1, auto t0, auto t1) {
+            if (r0 >= r1) return;
+            uint32_t w = table[r0];
             int row = s_row[8 + yt + sgy * (int)(int8_t)(w & 0xff)];
-            for (;;) {
+            for (int r = r0;;) {
                 // the next row's place is read while this one is worked on
-                const uint32_t wn = table[r + RS];
+                const uint32_t wn = table[r + 1];
                 const int next = s_row[8 + yt + sgy * (int)(int8_t)(wn & 0xff)];
-                const double2* src = lds2 + row + kRecUnits * (8 + xt) + step_x * (int)(int8_t)((w >> 8) & 0xff);
+                const double2* src = plane + row + kRecUnits * (8 + xt) + step_x * (int)(int8_t)((w >> 8) & 0xff);
                 const int n = (int)(w >> 16);
                 for (int k = 0; k < n; ++k, src += step_x) {
                     double f[2 * kRecUnits];
@@ -716,47 +813,79 @@ __global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
                     for (int t = t0; t < t1; ++t)
                         pair_sums<T::sums>(acc + t * T::nacc, f, xi[t] - f[0], yi[t] - f[1], zi[t] - f[2]);
                 }
-                r += RS;
-                if (r >= r1) break;
+                if (++r >= r1) break;
                 w = wn;
                 row = next;
             }
         };
 
         const int first = 4 + z0 / 2, last = 4 + (z0 + kPlanes - 1) / 2;  // the targets' parent planes
-        __syncthreads();  // s_rel is there
-        for (int ps = first - 4; ps <= last + 4; ++ps) {
-            // a layer of neighbours that are all missing holds no source
-            if ((ps & 3) == 0 || ps == first - 4) {
-                bool some = false;
-                for (int b = 0; b < 9; ++b) some |= s_rel[9 * (ps >> 2) + b].x >= 0;
-                if (!some) {
-                    ps |= 3;
-                    continue;
+        // the next plane from zs on that can hold a source in reach (a layer of
+        // neighbours that are all missing holds none), or -1
+        auto plane_from = [&](int zs) {
+            while (zs < 2 * (last + 4) + 2) {
+                if ((zs & 7) == 0 || zs == 2 * (first - 4)) {
+                    bool some = false;
+                    for (int b = 0; b < 9; ++b) some |= s_rel[9 * (zs >> 3) + b].x >= 0;
+                    if (!some) {
+                        zs = (zs | 7) + 1;
+                        continue;
+                    }
                 }
+                return zs;
             }
+            return -1;
+        };
+        auto reach2 = [&](int zs) {
+            const int ps = zs >> 1;
             const int gap = ps < first ? first - ps : (ps > last ? ps - last : 0);
-            const int reach2 = 16 - gap * gap;
-#pragma unroll 1
-            for (int zs = 2 * ps; zs < 2 * ps + 2; ++zs) {
-                __syncthreads();  // the previous plane is no longer read
-                stage_plane<MODE>(p, s_rel, zs, reach2, pk, lds2);
+            return 16 - gap * gap;
+        };
+        auto add_plane = [&](int zs, const double2* plane) {
+            const int e = zs - (8 + zt);
+            if (e < -kReach || e > kReach) return;
+            constexpr std::integral_constant<int, 0> c0{};
+            constexpr std::integral_constant<int, 1> c1{};
+            constexpr std::integral_constant<int, KZ> ck{};
+            const auto& share = c_shares<KZ, RS>;
+            if constexpr (KZ == 1) {
+                const int* rg = share.range[zt & 1][e + kReach][sub];
+                rows(plane, share.rows[zt & 1], rg[0], rg[1], c0, c1);
+            } else {
+                const int* rg = share.range[0][e + kReach][sub];
+                rows(plane, share.rows[0], rg[0], rg[1], c0, ck);
+                rows(plane, share.rows[0], rg[1], rg[2], c0, c1);
+                rows(plane, share.rows[0], rg[2], rg[3], c1, ck);
+            }
+        };
+        __syncthreads();  // s_rel is there
+        if constexpr (kAhead) {
+            int zs = plane_from(2 * (first - 4));
+            StagedCell ahead;
+            if (zs >= 0) load_cell<MODE>(p, s_rel, zs, reach2(zs), pk[0], ahead);
+            double2* plane = lds2;
+            while (zs >= 0) {
+                put_cell<MODE>(p, ahead, pk[0], plane);
+                const int next = plane_from(zs + 1);
+                if (next >= 0) load_cell<MODE>(p, s_rel, next, reach2(next), pk[0], ahead);
+                // every wavefront is past the plane before, whose buffer is written next
                 __syncthreads();
-                const int e = zs - (8 + zt);
-                if (e < -kReach || e > kReach) continue;
-                if constexpr (KZ == 1) {
-                    const int* rg = c_stencil.range[zt & 1][e + kReach];
-                    rows(c_stencil.rows[zt & 1], rg[0], rg[1], std::integral_constant<int, 0>{},
-                         std::integral_constant<int, 1>{});
-                } else {
-                    const int* rg = c_pair.range[e + kReach];
-                    rows(c_pair.rows, rg[0], rg[1], std::integral_constant<int, 0>{},
-                         std::integral_constant<int, KZ>{});
-                    rows(c_pair.rows, rg[1], rg[2], std::integral_constant<int, 0>{},
-                         std::integral_constant<int, 1>{});
-                    rows(c_pair.rows, rg[2], rg[3], std::integral_constant<int, 1>{},
-                         std::integral_constant<int, KZ>{});
+                add_plane(zs, plane);
+                plane = plane == lds2 ? lds2 + kPlaneUnits : lds2;
+                zs = next;
+            }
+        } else {
+#pragma unroll 1
+            for (int zs = plane_from(2 * (first - 4)); zs >= 0; zs = plane_from(zs + 1)) {
+                __syncthreads();  // the previous plane is no longer read
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    StagedCell c;
+                    load_cell<MODE>(p, s_rel, zs, reach2(zs), pk[it], c);
+                    put_cell<MODE>(p, c, pk[it], lds2);
                 }
+                __syncthreads();
+                add_plane(zs, lds2);
             }
         }
 
@@ -778,6 +907,25 @@ __global__ void __launch_bounds__(kThreads, 2) k_interact(const KParams p)
                     for (int w = 1; w < RS; ++w) sum[a] += from[(w * KZ * T::nacc + a) * 64];
                 }
                 store_sums<MODE>(p, owner, cell + 64 * sub, sum);
+            }
+        } else if constexpr (RS == 8) {
+            // the eighth of the sums that each wavefront adds up, then the first
+            if (sub > 0) {
+#pragma unroll
+                for (int a = 0; a < T::nacc; ++a) lds[((sub - 1) * T::nacc + a) * 64 + lane] = acc[a];
+            }
+            __syncthreads();
+            for (int a = sub; a < T::nacc; a += RS) {
+                double v = lds[a * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < RS - 1; ++w) v += lds[(w * T::nacc + a) * 64 + lane];
+                lds[a * 64 + lane] = v;
+            }
+            __syncthreads();
+            if (sub == 0) {
+#pragma unroll
+                for (int a = 0; a < T::nacc; ++a) acc[a] += lds[a * 64 + lane];
+                store_sums<MODE>(p, owner, cell, acc);
             }
         } else {
             double* mine = lds + (wave / RS) * (RS - 1) * T::nacc * 64;

@@ -1,6 +1,6 @@
 """The splits of the batched passes over the chip: a work-group per target
-cells (few targets), four or two wavefronts a target plane, ordinary and
-persistent launches, at the target counts where the choice changes; and the
+cells (few targets), eight, four or two wavefronts a target plane, ordinary
+and persistent launches, at the target counts where the choice changes; and the
 work counters of persistent launches (left at zero by every launch, two pools
 per plan). Oracle and criterion as in test_gpu_parity.py (1e-12 per sub-grid
 and output order)."""
@@ -47,13 +47,14 @@ def _nan(*shape):
 
 
 def _subset(k, seed):
-    """A store of k sub-grids drawn from a 4^3 lattice (periodic), all of them
-    targets; neighbours outside the draw are missing."""
+    """A store of k sub-grids drawn from a 4^3 (5^3) lattice (periodic), all of
+    them targets; neighbours outside the draw are missing."""
     rng = synthetic._rng(seed)
-    M, X = synthetic.store_field(4, rng, 2.0, 3.0, 0.6, sep=6.0)
-    full = synthetic.lattice_batch(4)
-    ids = np.sort(rng.permutation(64)[:k])
-    to = np.full(65, -1, np.int32)
+    side = 4 if k <= 64 else 5
+    M, X = synthetic.store_field(side, rng, 2.0, 3.0, 0.6, sep=6.0)
+    full = synthetic.lattice_batch(side)
+    ids = np.sort(rng.permutation(side ** 3)[:k])
+    to = np.full(side ** 3 + 1, -1, np.int32)
     to[ids] = np.arange(k)
     cols = (ids[:, None] * SUB3 + np.arange(SUB3)).reshape(-1)
     batch = {"S": k, "T": k, "tgt": np.arange(k, dtype=np.int32), "nbr": to[full["nbr"][ids]],
@@ -62,7 +63,7 @@ def _subset(k, seed):
 
 
 @pytest.mark.parametrize("full", [False, True])
-@pytest.mark.parametrize("k", [1, 2, 20, 21, 24, 25, 33, 64])
+@pytest.mark.parametrize("k", [1, 2, 20, 21, 24, 25, 33, 64, 96, 97])
 def test_every_split_matches_the_oracle(ot, k, full):
     batch, M, X = _subset(k, 400 + k)
     w = synthetic.weights(k, 500 + k)
