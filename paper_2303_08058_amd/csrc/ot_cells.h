@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(NT, NT == 512 ? 2 : 3) k_cells(const KParams p
     __shared__ double s_sum[kWaves][kN];
     __shared__ int4 s_rel[27];
     const int tid = threadIdx.x;
-    const int owner = (int)blockIdx.x / kGroups;
+    const int owner = p.first + (int)blockIdx.x / kGroups;
     const int g = (int)(blockIdx.x & 7u) * (kGroups / 8) + (((int)blockIdx.x % kGroups) >> 3);
     const int cell0 = KT * g;  // the group's first cell; a pair shares x / 2, y, z
     const int xt = cell0 & 7, yt = (cell0 >> 3) & 7, zt = cell0 >> 6;

@@ -148,6 +148,16 @@ constexpr int kCellOwners = 20;
 // against 461 / 481 / 810 / 804.
 constexpr int kWideRounds = 3;
 
+// Above that, and below the targets from which a persistent launch evens out
+// its end, time goes in steps of a round (a work-group of 4 wavefronts a CU: 64
+// targets of 256 CUs, 209 us forward, 425 with saved sums). The targets past
+// the last whole round go in a launch of their own if they are at most half a
+// round: eight wavefronts a plane take 114 us (205) for them, k_cells 7 (14) a
+// target. 150 targets forward 590 -> 528 us, 210 782 -> 720, 480 1544 -> 1488;
+// with saved sums 1195 -> 1035, 1594 -> 1431, 3173 -> 3039. The split depends on the
+// number of targets alone, so every schedule gives the same result.
+constexpr int kCellRest = 12;
+
 // Every shape selects the same kernel; the tuners try the flags on this one.
 constexpr int kTunedShape = OT_FMM_SCHED_W8;
 
@@ -377,16 +387,25 @@ int launch_parts(KParams kp, int owners, int* counter, int n_cu, hipStream_t str
     }
     return launch<MODE, KZ, RS, false>(kp, (int)items, stream);
 }
+
 template <int MODE>
 int launch_any(const KParams& kp, int owners, int* counter, int n_cu, hipStream_t stream)
 {
     if (owners <= kCellOwners) return launch_cells<MODE>(kp, owners, stream);
     if (owners * (int64_t)kSub <= (int64_t)kWideRounds * n_cu)
         return launch_parts<MODE, 1, 8>(kp, owners, nullptr, n_cu, stream);  // too few entries to deal out
-    if constexpr (planes_per_wave<MODE>() == 2)
-        return launch_parts<MODE, 2, 4>(kp, owners, counter, n_cu, stream);
-    else
-        return launch_parts<MODE, 1, 2>(kp, owners, counter, n_cu, stream);
+    constexpr int kz = planes_per_wave<MODE>(), rs = 2 * kz;
+    const int round = n_cu / parts_per_target(kz, rs);
+    const int rest = round > 0 ? owners % round : 0;
+    if (owners >= kPersistentOwners || rest == 0 || 2 * rest > round)
+        return launch_parts<MODE, kz, rs>(kp, owners, counter, n_cu, stream);
+    KParams part = kp;
+    part.order = nullptr;
+    int rc = launch_parts<MODE, kz, rs>(part, owners - rest, nullptr, n_cu, stream);
+    if (rc) return rc;
+    part.first = owners - rest;
+    return rest <= kCellRest ? launch_cells<MODE>(part, rest, stream)
+                             : launch_parts<MODE, 1, 8>(part, rest, nullptr, n_cu, stream);
 }
 
 // The work order of a launch: XCD-aware (OT_FMM_SCHED_LOCAL) or longest work

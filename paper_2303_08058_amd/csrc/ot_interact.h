@@ -259,7 +259,8 @@ struct KParams {
     long pos_stride;
     const int4* rel;       // [owners][27]: {moment block, position block, packed shift, 0}
     const int* own_blk;    // owner -> store block of its own cells (NULL: identity)
-    const int* order;      // work-group -> owner (NULL: identity)
+    const int* order;      // work-group -> owner (NULL: from `first` on)
+    int first;             // with no order: the first owner of the launch
     const double* aux;     // epilogue input: gL (B1) or M (B2), [20][aux_stride]
     long aux_stride;
     // B2S epilogue, the target role of the owner's cells: store sub-grid ->
@@ -774,7 +775,7 @@ __global__ void __launch_bounds__(64 * group_waves(RS), 2) k_interact(const KPar
             index = item % (p.n_items / kParts);
             part = item / (p.n_items / kParts);
         }
-        const int owner = p.order ? p.order[index] : index;
+        const int owner = p.order ? p.order[index] : p.first + index;
         if (tid < 27) s_rel[tid] = p.rel[(long)owner * 27 + tid];
         const int z0 = part * kPlanes;                 // first target plane of the work-group
         const int zt = z0 + KZ * (wave / RS);          // of the wavefront

@@ -1,6 +1,6 @@
 """The splits of the batched passes over the chip: a work-group per target
-cells (few targets), eight, four or two wavefronts a target plane, ordinary
-and persistent launches, at the target counts where the choice changes; and the
+cells (few targets), eight, four or two wavefronts a target plane, a launch of
+their own for the targets past whole rounds, ordinary and persistent launches, at the target counts where the choice changes; and the
 work counters of persistent launches (left at zero by every launch, two pools
 per plan). Oracle and criterion as in test_gpu_parity.py (1e-12 per sub-grid
 and output order)."""
@@ -47,10 +47,10 @@ def _nan(*shape):
 
 
 def _subset(k, seed):
-    """A store of k sub-grids drawn from a 4^3 (5^3) lattice (periodic), all of
+    """A store of k sub-grids drawn from a 4^3 to 6^3 lattice (periodic), all of
     them targets; neighbours outside the draw are missing."""
     rng = synthetic._rng(seed)
-    side = 4 if k <= 64 else 5
+    side = 4 if k <= 64 else 5 if k <= 125 else 6
     M, X = synthetic.store_field(side, rng, 2.0, 3.0, 0.6, sep=6.0)
     full = synthetic.lattice_batch(side)
     ids = np.sort(rng.permutation(side ** 3)[:k])
@@ -63,7 +63,7 @@ def _subset(k, seed):
 
 
 @pytest.mark.parametrize("full", [False, True])
-@pytest.mark.parametrize("k", [1, 2, 20, 21, 24, 25, 33, 64, 96, 97])
+@pytest.mark.parametrize("k", [1, 2, 20, 21, 24, 25, 33, 64, 96, 97, 130, 160])
 def test_every_split_matches_the_oracle(ot, k, full):
     batch, M, X = _subset(k, 400 + k)
     w = synthetic.weights(k, 500 + k)
@@ -115,6 +115,21 @@ def test_launch_forms_agree_bitwise(ot):
                 ref = (L, Ls, Cs, gM, gX)
             for a, r in zip((L, Ls, Cs, gM, gX), ref):
                 assert torch.equal(a, r), (sched, rep)
+
+
+def test_launch_forms_agree_with_a_rest(ot):
+    """216 targets: 192 in whole rounds, 24 in a launch of their own, the same
+    ones whatever the schedule's order."""
+    b, plan, M, X, torch = _lattice(ot, 6)
+    N = b["T"] * SUB3
+    ref = None
+    for sched in (1, 0x11, 0x21, 0x31, 0):
+        L, Ls, Cs = _nan(20, N), _nan(20, N), _nan(24, N)
+        plan.multipole_batched(M, X, L, sched=sched)
+        plan.multipole_batched_save(M, X, Ls, Cs, sched=sched)
+        torch.cuda.synchronize()
+        ref = ref or (L, Ls, Cs)
+        assert all(torch.equal(a, r) for a, r in zip((L, Ls, Cs), ref)), sched
 
 
 def test_auto_on_more_streams_than_counters(ot):
