@@ -40,26 +40,20 @@ PEAK_FP64_TFLOPS = 78.6  # 256 CUs x 128 FP64 FLOP/clk x 2.4 GHz
 # step 780.
 METHOD_FLOP = {"forward": 224, "adjoint": 556, "step": 780}
 
-# Per-launch counts of this implementation (secondary): the plain formulas
-# each kernel evaluates -- derivatives of 1/r to order 3 (incl. r = X_i - X_j):
-# 61, to order 4: 121; forward contraction 84 FMA; adjoint source-role pass
-# 84 + 111 FMA; target-role pass 64 + 111 FMA. The two adjoint passes each
-# evaluate the order-4 derivatives and the position-gradient terms, so their
-# sum (982) exceeds the method's 556.
+# FP64 operations per pair that this implementation executes (secondary),
+# counted in the pair loops of the compiled kernels (FMA = 2): the contraction
+# is arranged around the separation vector, with trace-free sources, so they
+# are fewer than the method's formulas (derivatives of 1/r, then products)
+# would take. The forward that saves the target-side sums, the one-pass
+# adjoint, the source-role pass and the forward with the angular-momentum
+# correction run the same loop.
 FLOP_PER_PAIR = {
-    "forward": 61 + 2 * 84,                # 229
-    "adjoint_source": 121 + 2 * (84 + 111),  # 511
-    "adjoint_target": 121 + 2 * (64 + 111),  # 471
-    # the two-launch step: the forward that saves the target-side sums
-    # evaluates the order-4 derivatives, the forward contraction (84 FMA) and
-    # the order-4 terms of orders 1..4 (111 FMA); the one-pass adjoint is the
-    # source-role pass (its per-cell epilogue adds the target role)
-    "forward_save": 121 + 2 * (84 + 111),    # 511
-    "adjoint_saved": 121 + 2 * (84 + 111),   # 511
-    # the forward with the angular-momentum correction: the same pair loop as
-    # the forward with saved sums (a per-cell epilogue contracts the order-4
-    # sums with the target's moments)
-    "forward_amc": 121 + 2 * (84 + 111),     # 511
+    "forward": 154,         # 95 instructions
+    "adjoint_source": 335,  # 202
+    "adjoint_target": 283,  # 171
+    "forward_save": 335,
+    "adjoint_saved": 335,
+    "forward_amc": 335,
 }
 
 
@@ -116,15 +110,15 @@ def main():
     ap.add_argument("--full-steps", type=int, default=2,
                     help="timed launches of the full-truncation forward (0: skip)")
     ap.add_argument("--full-sched", type=lambda v: int(v, 0), default=None,
-                    help="schedule of the full-truncation forward (default: fastest of the library default W8P2+persistent+xcd-local, W8 and W8P2)")
+                    help="schedule of the full-truncation forward (default: the faster of W8+persistent+xcd-local, the library's own choice, and W8)")
     ap.add_argument("--no-two-level", action="store_true",
                     help="skip the two-level step (its parent-level forward shares the forward kernel)")
     ap.add_argument("--fwd-sched", type=lambda v: int(v, 0), default=None,
-                    help="forward schedule code (skips the autotuner; e.g. 0x22 = W16 + XCD-local order)")
+                    help="forward schedule code (skips the autotuner; e.g. 0x31 = W8 + persistent + XCD-local order)")
     ap.add_argument("--bwd-sched", type=lambda v: int(v, 0), default=None,
                     help="backward schedule code, target role | source role << 8 (with --fwd-sched)")
     ap.add_argument("--save-sched", type=lambda v: [int(x, 0) for x in v.split(",")], default=None,
-                    help="schedules of the two-launch step, forward,adjoint (skips its autotuner; e.g. 0x33,0x33)")
+                    help="schedules of the two-launch step, forward,adjoint (skips its autotuner; e.g. 0x31,0x31)")
     ap.add_argument("--no-two-pass", action="store_true",
                     help="skip the three-launch step (plain forward, two adjoint passes)")
     ap.add_argument("--copy-calibration", action="store_true",
@@ -255,7 +249,7 @@ def main():
     plan.set_timing(False)
     del dF
     if fs is None:
-        fs = sf  # forward schedule of the two-level step (W8 / W8P2 also serve the plain forward)
+        fs = sf  # forward schedule of the two-level step
     # roofline: the step's two launches together, at the method's 780 FLOP per
     # pair (the forward's 224 and the adjoint's 556): the forward launch does
     # part of the adjoint's work, so neither launch alone has a method count
@@ -467,31 +461,24 @@ def tree_passes(n, steps, Md, Xd, L, ot, synthetic, np, torch, dev, plan=None, b
     return out
 
 
-# FP64 operations per cell pair of the full-truncation forward (every output
-# |a| <= 3 keeps every moment |b| <= 3; derivatives to order 6):
-#   as the kernel evaluates it -- r, 1/r and the radial factors D_0..D_6: 21;
-#   the derivative recursion over the 64 derivatives the trace-reduced
-#   contraction reads: 223; 16 x 16 reduced products: 512           -> 756
-#   plain formulas -- all 84 derivatives by the same recursion (443 + 21) and
-#   all 20 x 20 products (800)                                       -> 1264
-# The plain count overstates the executed work by 1.67x (its rate would pass
-# the hardware peak), so the roofline uses the reduced count.
-FULL_FLOP_REDUCED = 756
+# FP64 operations per cell pair of the full truncation (every output |a| <= 3
+# keeps every moment |b| <= 3; derivatives to order 6, 7 in the adjoint) as the
+# kernels execute them (pair loops of the compiled kernels, FMA = 2): forward
+# 196 instructions, source-role pass 302, target-role pass 298. Plain formulas
+# for the forward -- all 84 derivatives by recursion (443 + 21) and all 20 x 20
+# products (800) -- would take 1264; their rate would pass the hardware peak, so
+# the roofline uses the executed count.
+FULL_FLOP_REDUCED = 323
 FULL_FLOP_PLAIN = 1264
-# its adjoint (derivatives to order 7), counted the same way for the reduced
-# formulas: r, 1/r and D_0..D_7: 23; the derivative recursion over the 85 (84)
-# derivatives the contraction reads: 330; the reduced products: 25 x 16
-# (24 x 16) -> source-role pass 1153, target-role pass 1121
-FULL_ADJ_FLOP_REDUCED = 1153 + 1121
-# the two-launch step of the full truncation: the forward that also keeps the
-# target-side sums runs the source-role pass's pair loop (orders 0..4 from
-# every moment, 1153), and so does the one-pass adjoint
-FULL_SAVED_STEP_FLOP_REDUCED = 1153 + 1153
+FULL_ADJ_FLOP_REDUCED = 498 + 490
+# the two-launch step: the forward that also keeps the target-side sums and the
+# one-pass adjoint both run the source-role pass's pair loop
+FULL_SAVED_STEP_FLOP_REDUCED = 498 + 498
 
 
 def full_truncation(plan, pairs, steps, Md, Xd, L, ot, torch, sched=None, wd=None, gM=None, gX=None):
     """Times the full-truncation forward on the benchmark plan: the given
-    schedule, or the fastest of three over one launch each, then `steps`
+    schedule, or the faster of two over one launch each, then `steps`
     timed launches (HIP events on the launch stream); with weights and
     gradient arrays also its adjoint (both passes with the library's default
     schedule)."""
@@ -508,8 +495,8 @@ def full_truncation(plan, pairs, steps, Md, Xd, L, ot, torch, sched=None, wd=Non
         torch.cuda.synchronize()
         return e0.elapsed_time(e1) / n
 
-    default = ot.SCHED_W8P2 | ot.SCHED_PERSISTENT | ot.SCHED_LOCAL  # the library's AUTO for this truncation
-    cands = {sc: sched_name(sc) for sc in (default, ot.SCHED_W8, ot.SCHED_W8P2)}
+    default = ot.SCHED_W8 | ot.SCHED_PERSISTENT | ot.SCHED_LOCAL  # what the library's AUTO takes for this many
+    cands = {sc: sched_name(sc) for sc in (default, ot.SCHED_W8)}
     if sched is not None:
         cands = {sched: sched_name(sched)}
     plan.multipole_batched_full(Md, Xd, L, sched=next(iter(cands)))  # warm-up
