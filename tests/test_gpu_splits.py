@@ -89,6 +89,32 @@ def test_every_split_matches_the_oracle(ot, k, full):
     assert_parity(pick(gX2), gX_ref, TOL, what="k=%d three-launch gX" % k)
 
 
+def test_subset_of_targets_with_a_rest(ot):
+    """150 of 216 sub-grids are targets, in no order: a rest of 22 targets and,
+    in the source role, of 24 sub-grids."""
+    batch, M, X = _subset(216, 616)
+    k = 150
+    tgt = synthetic._rng(617).permutation(216)[:k].astype(np.int32)
+    batch.update(T=k, tgt=tgt, nbr=np.ascontiguousarray(batch["nbr"][tgt]),
+                 shift=np.ascontiguousarray(batch["shift"][tgt]))
+    w = synthetic.weights(k, 618)
+    plan = ot.Plan.from_batch(batch)
+    Md, Xd, wd = _dev(M), _dev(X), _dev(w)
+    L, Cs = _nan(20, k * SUB3), _nan(24, k * SUB3)
+    gM, gX = _nan(20, 216 * SUB3), _nan(3, 216 * SUB3)
+    plan.multipole_batched_save(Md, Xd, L, Cs)
+    plan.multipole_backward_saved(Md, Xd, wd, Cs, gM, gX)
+    sel = np.array([0, 127, 128, 149], np.int32)
+    pick = lambda t, n, i: _host(t).reshape(t.shape[0], n, SUB3)[:, i].reshape(t.shape[0], -1)  # noqa: E731
+    ref, A = oracle.batched_forward(batch, M, X, tsel=sel, want_abs=True)
+    assert_parity(pick(L, k, sel), ref, TOL, what="L", A=A)
+    check_saved(pick(Cs, k, sel), batch, M, X, "Cs", tsel=sel)
+    ssel = np.array([0, 191, 192, 215], np.int32)
+    gM_ref, gX_ref = oracle.batched_backward(batch, M, X, w, ssel=ssel)
+    assert_parity(pick(gM, 216, ssel), gM_ref, TOL, what="gM")
+    assert_parity(pick(gX, 216, ssel), gX_ref, TOL, what="gX")
+
+
 def _lattice(ot, n, missing=0.2, seed=41):
     """A large lattice of cheap inputs (values do not matter for equality)."""
     import torch
