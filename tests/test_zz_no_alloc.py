@@ -160,3 +160,22 @@ def test_pieces_per_xcd_change_nothing(ot):
         ot.ot_fmm_multipole_batched_noalloc(729, 729, dev["tgt"], dev["nbr"], dev["shift"], b["period"], M, X, L)
     ot.Plan.from_batch(b).multipole_batched(M, X, R, sched=1)
     assert torch.equal(L, R)
+
+
+def test_rest_in_a_launch_of_its_own(ot):
+    """216 targets: 192 in whole rounds and 24 in a second launch, bitwise the
+    plan's; an invalid entry makes the outputs of both NaN."""
+    import torch
+    b = synthetic.apply_missing(synthetic.lattice_batch(6), 0.2, synthetic._rng(47))
+    M, X = synthetic.device_lattice_store(6, 47)
+    dev = {k: torch.from_numpy(np.ascontiguousarray(b[k])).cuda() for k in ("tgt", "nbr", "shift")}
+    L = torch.zeros((20, 216 * 512), dtype=torch.float64, device="cuda")
+    R = torch.full_like(L, float("nan"))
+    bad = dev["nbr"].clone()
+    bad[5, 2] = 216
+    ot.ot_fmm_multipole_batched_noalloc(216, 216, dev["tgt"], bad, dev["shift"], b["period"], M, X, L)
+    assert ot.ot_fmm_noalloc_status() == (1, 5 * 27 + 2)
+    assert bool(torch.isnan(L).all())
+    ot.ot_fmm_multipole_batched_noalloc(216, 216, dev["tgt"], dev["nbr"], dev["shift"], b["period"], M, X, L)
+    ot.Plan.from_batch(b).multipole_batched(M, X, R, sched=ot.SCHED_W16 | ot.SCHED_PERSISTENT)
+    assert torch.equal(L, R)
