@@ -208,18 +208,21 @@ constexpr int kOptional = 0x100;
 // targets (or store sub-grids) on, an ordinary launch, longest work first,
 // below. The pieces cut the staging traffic (forward of 16384 sub-grids 57.8
 // -> 52.6 ms, 4096: 14.2 -> 13.4); with few work-groups a CU they end less
-// evenly (512: 1.69 -> 1.83 ms).
+// evenly (forward of 576: 1.85 -> 1.91 ms, both adjoint passes 6.93 -> 7.28). The
+// two launches of the saved sums gain from 449 on (486: 3.26 + 3.31 -> 3.19 + 3.24
+// ms, 567: 3.67 + 3.73 -> 3.60 + 3.69; 448, 512 and 576, whole rounds, unchanged).
 constexpr int kPersistentOwners = 640;
+constexpr int kPersistentOwnersSaved = 449;
 
 // kernels timed by the plan's events (ot_fmm_plan_kernel_times)
 constexpr int kTimedKernels = OT_FMM_NKERNELS;
 
 // The schedule of one pass over `owners` targets or store sub-grids.
-int pick(int sched, int tuned, int owners)
+int pick(int sched, int tuned, int owners, int persistent_from)
 {
     if (sched != OT_FMM_SCHED_AUTO) return sched;
     if (tuned) return tuned;
-    return owners >= kPersistentOwners
+    return owners >= persistent_from
                ? (OT_FMM_SCHED_W8 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL | kOptional)
                : OT_FMM_SCHED_W8;
 }
@@ -458,7 +461,7 @@ int fwd_batched(ot_fmm_plan plan, const double* M, const double* com, double* L,
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, plan->T), stream);
+    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, plan->T, kPersistentOwners), stream);
 }
 
 // Forward with the full truncation: the same plan, tables and schedules as
@@ -478,7 +481,7 @@ int fwd_full_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_FULL_STORE>(plan, -1, kp, pick(sched, 0, plan->T), stream);
+    return launch_timed<MODE_FULL_STORE>(plan, -1, kp, pick(sched, 0, plan->T, kPersistentOwners), stream);
 }
 
 // Adjoint of the batched forward (FULL: of the full truncation, with
@@ -497,8 +500,8 @@ int bwd_any(ot_fmm_plan plan, const double* M, const double* com, const double* 
     int tsched = sched & 0xff, ssched = (sched >> 8) & 0xff;
     if (FULL && (tsched & kShapeMask) == OT_FMM_SCHED_W16)
         return fail(OT_FMM_EINVAL, "16 wavefronts are not available for the full truncation's adjoint");
-    tsched = pick(tsched, FULL ? 0 : plan->tuned_bwd & 0xff, plan->T);
-    ssched = pick(ssched, FULL ? 0 : plan->tuned_bwd >> 8, plan->S);
+    tsched = pick(tsched, FULL ? 0 : plan->tuned_bwd & 0xff, plan->T, kPersistentOwners);
+    ssched = pick(ssched, FULL ? 0 : plan->tuned_bwd >> 8, plan->S, kPersistentOwners);
     const long NS = (long)plan->S * kSub3, NT = (long)plan->T * kSub3;
     // source role: owners are store sub-grids, sources the target cells that see them
     KParams b2{};
@@ -575,7 +578,8 @@ int fwd_save_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<kMode>(plan, FULL ? -1 : 3, kp, pick(sched, FULL ? 0 : plan->tuned_save, plan->T), stream);
+    return launch_timed<kMode>(plan, FULL ? -1 : 3, kp,
+                               pick(sched, FULL ? 0 : plan->tuned_save, plan->T, kPersistentOwnersSaved), stream);
 }
 
 // Forward with the angular-momentum correction of the force: L, and
@@ -599,7 +603,8 @@ int fwd_amc_batched(ot_fmm_plan plan, const double* M, const double* com, double
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_AMC_STORE>(plan, 5, kp, pick(sched, plan->tuned_save, plan->T), stream);
+    return launch_timed<MODE_AMC_STORE>(plan, 5, kp, pick(sched, plan->tuned_save, plan->T, kPersistentOwnersSaved),
+                                        stream);
 }
 
 // One-pass adjoint from the saved sums: the source-role pass over every store
@@ -630,8 +635,8 @@ int bwd_saved_batched(ot_fmm_plan plan, const double* M, const double* com, cons
     kp.out_stride = NS;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<kMode>(plan, FULL ? -1 : 4, kp, pick(sched, FULL ? 0 : plan->tuned_saved_bwd, plan->S),
-                               stream);
+    return launch_timed<kMode>(plan, FULL ? -1 : 4, kp,
+                               pick(sched, FULL ? 0 : plan->tuned_saved_bwd, plan->S, kPersistentOwnersSaved), stream);
 }
 
 int check_plan(ot_fmm_plan plan)

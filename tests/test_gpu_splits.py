@@ -143,10 +143,12 @@ def test_launch_forms_agree_bitwise(ot):
                 assert torch.equal(a, r), (sched, rep)
 
 
-def test_launch_forms_agree_with_a_rest(ot):
+@pytest.mark.parametrize("n", [6, 8])
+def test_launch_forms_agree_with_a_rest(ot, n):
     """216 targets: 192 in whole rounds, 24 in a launch of their own, the same
-    ones whatever the schedule's order."""
-    b, plan, M, X, torch = _lattice(ot, 6)
+    ones whatever the schedule's order. 512: AUTO is persistent for the saved
+    sums only."""
+    b, plan, M, X, torch = _lattice(ot, n)
     N = b["T"] * SUB3
     ref = None
     for sched in (1, 0x11, 0x21, 0x31, 0):
