@@ -77,10 +77,11 @@ enum {
      * are resident at once, taking work-list entries (longest first) from
      * counters that every launch leaves at zero for the next one. The
      * counters are never shared by launches that can overlap: eager launches
-     * use one set per stream (up to 64 streams per plan), launches recorded
-     * into a graph a set of their own (up to 960 per plan over its life; the
-     * plan's own step graph returns its sets when it is replaced). Beyond
-     * either limit the call returns OT_FMM_EINVAL. */
+     * use one set per stream (up to 64 streams per plan; on a 65th the call
+     * returns OT_FMM_EINVAL), the plan's own step graph sets of its own (its
+     * replays run one after the other, whatever their streams). Launches on
+     * hipStreamPerThread and launches recorded into a caller's graph, which
+     * may be instantiated more than once, are ordinary ones. */
     OT_FMM_SCHED_PERSISTENT = 0x10,
     /* flag, OR-ed into a schedule: XCD-aware work order -- entries sorted
      * along a Morton curve of the lattice positions recovered from the

@@ -187,19 +187,22 @@ bool valid_bwd_sched(int s)
 // kMaxPieces counters that no launch able to run at the same time shares; the
 // launch leaves them zero (see k_interact), so a slot is ready for the next:
 //  * eager launches: one slot per stream -- launches on one stream run in
-//    order (kEagerSlots streams per plan);
-//  * launches recorded into a graph (the stream is capturing): a slot of
-//    their own that no other launch is given, since the graph may be
-//    replayed at any time until it is destroyed, which the library cannot
-//    see (kCaptureSlots per plan); the slots of the plan's own step graph
-//    return to the pool when that graph is replaced.
-// Launches that AUTO makes persistent have a pool of the same size of their
-// own, and run as ordinary launches once it is used up: they never take a
-// slot from a launch whose schedule asks for one.
+//    order, and destroying a stream waits for its work, so that a new stream
+//    with the old one's handle starts after it (kEagerSlots streams per plan).
+//    hipStreamPerThread is one handle for a stream of every thread, so
+//    launches on it have no slot;
+//  * the plan's own step graph: a slot per launch. The plan holds its only
+//    executable and orders its replays (ot_fmm_step_graph_launch);
+//  * launches recorded into a caller's graph have none: it may be instantiated
+//    several times and its executables replayed side by side, which the
+//    library cannot see.
+// A persistent launch without a slot runs as an ordinary one, with the same
+// results. Launches that AUTO makes persistent have a pool of the same size of
+// their own, and run as ordinary launches once it is used up: they never take
+// a slot from a launch whose schedule asks for one.
 constexpr int kEagerSlots = 64;
-constexpr int kCaptureSlots = 960;
-constexpr int kPoolSlots = kEagerSlots + kCaptureSlots;
-constexpr int kCounterSlots = 2 * kPoolSlots;
+constexpr int kGraphSlots = 3;  // forward and two adjoint passes
+constexpr int kCounterSlots = 2 * kEagerSlots + kGraphSlots;
 
 // A schedule that AUTO stands for may be given up for an ordinary launch.
 constexpr int kOptional = 0x100;
@@ -253,22 +256,19 @@ struct ot_fmm_plan_s {
     int rev_piece_off[kMaxPieces + 1] = {0};
     int tuned_fwd = 0, tuned_bwd = 0;
     int tuned_save = 0, tuned_saved_bwd = 0;  // forward with saved sums, one-pass adjoint
-    // persistent launches: kMaxPieces work counters per slot, two pools of
-    // slots (see counter_slot), in each [0, kEagerSlots) of streams (eager
-    // launches) and the others of launches recorded into graphs
+    // persistent launches: kMaxPieces work counters per slot -- two pools of
+    // kEagerSlots, then the step graph's (see counter_slot)
     int* d_counters = nullptr;  // [kCounterSlots][kMaxPieces]
     std::mutex slot_mutex;
-    struct SlotPool {
-        std::vector<std::pair<hipStream_t, int>> stream_slot;  // eager: stream -> slot
-        int next_capture = 0;           // capture slots handed out so far
-        std::vector<int> free_capture;  // capture slots returned by replaced step graphs
-    } pool[2];
-    std::vector<int> graph_slots;          // capture slots of the plan's step graph
-    std::vector<int>* capture_log = nullptr;  // collects them while it is captured
-    hipStream_t capture_stream = nullptr;     // on this stream
+    std::vector<std::pair<hipStream_t, int>> stream_slot[2];  // eager: stream -> slot
+    hipStream_t capture_stream = nullptr;  // while the step graph is captured: on this stream,
+    int graph_launches = 0;                // with so many counter slots taken
     int n_cu = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
+    bool graph_counted = false;           // its launches take counters: replays in order
+    hipEvent_t graph_done = nullptr;      // the last such replay
+    std::mutex graph_mutex;
     // per-kernel timing (forward, adjoint source pass, adjoint target pass,
     // forward with saved sums, one-pass adjoint, forward with the
     // angular-momentum correction)
@@ -329,43 +329,36 @@ int resident_per_cu()
     return n;
 }
 
-// The counter slot of a persistent launch on `stream` (rules above); optional:
-// from the second pool, and *out stays NULL where that has none left.
+// The counter slot of a persistent launch on `stream`, or NULL in *out for an
+// ordinary launch (rules above); optional: from the second pool, and NULL where
+// that has none left.
 int counter_slot(ot_fmm_plan plan, hipStream_t stream, bool optional, int** out)
 {
+    *out = nullptr;
+    if (stream == hipStreamPerThread) return OT_FMM_OK;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     OT_HIP(hipStreamIsCapturing(stream, &st));
     std::lock_guard<std::mutex> lock(plan->slot_mutex);
-    auto& pool = plan->pool[optional ? 1 : 0];
-    const int base = optional ? kPoolSlots : 0;
     int slot = -1;
     if (st != hipStreamCaptureStatusNone) {
-        if (!pool.free_capture.empty()) {
-            slot = pool.free_capture.back();
-            pool.free_capture.pop_back();
-        } else if (pool.next_capture < kCaptureSlots) {
-            slot = base + kEagerSlots + pool.next_capture++;
-        } else if (optional) {
+        if (!plan->capture_stream || stream != plan->capture_stream || plan->graph_launches >= kGraphSlots)
             return OT_FMM_OK;
-        } else {
-            return fail(OT_FMM_EINVAL, "more persistent launches recorded into graphs than the plan's "
-                                       "960 counter slots; use a non-persistent schedule or a new plan");
-        }
-        if (plan->capture_log && stream == plan->capture_stream) plan->capture_log->push_back(slot);
+        slot = 2 * kEagerSlots + plan->graph_launches++;
     } else {
-        for (const auto& e : pool.stream_slot)
+        auto& pool = plan->stream_slot[optional ? 1 : 0];
+        for (const auto& e : pool)
             if (e.first == stream) {
                 slot = e.second;
                 break;
             }
         if (slot < 0) {
-            if ((int)pool.stream_slot.size() >= kEagerSlots) {
+            if ((int)pool.size() >= kEagerSlots) {
                 if (optional) return OT_FMM_OK;
                 return fail(OT_FMM_EINVAL, "persistent launches of one plan on more than 64 streams; use a "
                                            "non-persistent schedule or another plan");
             }
-            slot = base + (int)pool.stream_slot.size();
-            pool.stream_slot.emplace_back(stream, slot);
+            slot = (optional ? kEagerSlots : 0) + (int)pool.size();
+            pool.emplace_back(stream, slot);
         }
     }
     *out = plan->d_counters + (size_t)slot * kMaxPieces;
@@ -658,6 +651,7 @@ void free_plan_memory(ot_fmm_plan p)
         }
     if (p->graph_exec) (void)hipGraphExecDestroy(p->graph_exec);
     if (p->graph) (void)hipGraphDestroy(p->graph);
+    if (p->graph_done) (void)hipEventDestroy(p->graph_done);
     p->graph_exec = nullptr;
     p->graph = nullptr;
     (void)hipFree(p->d_fwd_rel);
@@ -894,8 +888,7 @@ int build_host_tables(int32_t S, int32_t T, const int32_t* tgt, const int32_t* n
 
 namespace {
 // Captures the launches `enqueue(stream)` makes into the plan's step graph
-// (replacing any previous one): the counter slots its persistent launches
-// take belong to the graph and return to the pool when it is replaced.
+// (replacing any previous one).
 template <class F>
 int capture_step_graph(ot_fmm_plan plan, F&& enqueue)
 {
@@ -909,59 +902,44 @@ int capture_step_graph(ot_fmm_plan plan, F&& enqueue)
     }
     const bool timing = plan->timing;
     plan->timing = false;  // no timing events inside the graph
-    std::vector<int> slots;  // counter slots the captured launches take
     {
         std::lock_guard<std::mutex> lock(plan->slot_mutex);
-        plan->capture_log = &slots;
         plan->capture_stream = cs;
+        plan->graph_launches = 0;
     }
     int rc = enqueue(cs);
     plan->timing = timing;
+    bool counted;
     {
         std::lock_guard<std::mutex> lock(plan->slot_mutex);
-        plan->capture_log = nullptr;
         plan->capture_stream = nullptr;
+        counted = plan->graph_launches > 0;
     }
-    // slots of a graph that is never instantiated go back to their pools
-    auto give_back = [&](const std::vector<int>& v) {
-        std::lock_guard<std::mutex> lock(plan->slot_mutex);
-        for (int slot : v) plan->pool[slot >= kPoolSlots ? 1 : 0].free_capture.push_back(slot);
-    };
     e = hipStreamEndCapture(cs, &g);
     (void)hipStreamDestroy(cs);
     if (rc) {
         if (g) (void)hipGraphDestroy(g);
-        give_back(slots);
         return rc;
     }
-    if (e != hipSuccess) {
-        give_back(slots);
-        return hip_fail(e, "hipStreamEndCapture");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
     hipGraphExec_t ex = nullptr;
     e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
+    if (e == hipSuccess && counted && !plan->graph_done)
+        e = hipEventCreateWithFlags(&plan->graph_done, hipEventDisableTiming);
+    // a replay of the graph being replaced may still run, with the counters
+    // that the new one takes
+    if (e == hipSuccess && plan->graph_exec) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
+        if (ex) (void)hipGraphExecDestroy(ex);
         (void)hipGraphDestroy(g);
-        give_back(slots);
-        return hip_fail(e, "hipGraphInstantiate");
+        return hip_fail(e, "step graph");
     }
-    if (plan->graph_exec) {
-        // a replay of the graph being replaced may still run: its counter
-        // slots are reused only once the device is idle
-        e = hipDeviceSynchronize();
-        if (e != hipSuccess) {
-            (void)hipGraphExecDestroy(ex);
-            (void)hipGraphDestroy(g);
-            give_back(slots);
-            return hip_fail(e, "hipDeviceSynchronize");
-        }
-        (void)hipGraphExecDestroy(plan->graph_exec);
-        give_back(plan->graph_slots);
-    }
+    std::lock_guard<std::mutex> lock(plan->graph_mutex);
+    if (plan->graph_exec) (void)hipGraphExecDestroy(plan->graph_exec);
     if (plan->graph) (void)hipGraphDestroy(plan->graph);
     plan->graph = g;
     plan->graph_exec = ex;
-    plan->graph_slots.swap(slots);
+    plan->graph_counted = counted;
     return OT_FMM_OK;
 }
 
@@ -1733,8 +1711,18 @@ int ot_fmm_step_graph_launch(ot_fmm_plan plan, void* stream)
     g_last_error.clear();
     int rc = check_plan(plan);
     if (rc) return rc;
+    std::lock_guard<std::mutex> lock(plan->graph_mutex);
     if (!plan->graph_exec) return fail(OT_FMM_EINVAL, "no step graph captured");
-    OT_HIP(hipGraphLaunch(plan->graph_exec, (hipStream_t)stream));
+    // replays share the graph's work counters: each after the one before, also
+    // where that is on another stream (a replay is not captured: it leaves the
+    // graph of a capturing stream empty, and no event is recorded into that)
+    hipStream_t s = (hipStream_t)stream;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (plan->graph_counted) OT_HIP(hipStreamIsCapturing(s, &st));
+    const bool ordered = plan->graph_counted && st == hipStreamCaptureStatusNone;
+    if (ordered) OT_HIP(hipStreamWaitEvent(s, plan->graph_done, 0));
+    OT_HIP(hipGraphLaunch(plan->graph_exec, s));
+    if (ordered) OT_HIP(hipEventRecord(plan->graph_done, s));
     return OT_FMM_OK;
 }
 

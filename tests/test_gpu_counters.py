@@ -1,0 +1,166 @@
+"""Work counters of persistent launches are never shared by launches that can
+overlap: launches of several threads on hipStreamPerThread, several executables
+of one captured graph, replays of the plan's step graph on several streams.
+729 targets (a periodic lattice of 9^3 sub-grids), where AUTO is persistent and
+the launches take long enough to overlap. The expected outputs are those of the
+ordinary launches, bit for bit (the schedules share one split of the work; the
+kernels are compared with the oracle in the other files)."""
+import ctypes
+import os
+import sys
+import threading
+
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+import synthetic  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+N = 729 * 512
+PER_THREAD = 2  # the handle hipStreamPerThread
+
+
+@pytest.fixture(scope="module")
+def ot():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2303_08058_amd as mod
+    return mod
+
+
+def _nan(k):
+    import torch
+    return torch.full((k, N), float("nan"), dtype=torch.float64, device="cuda")
+
+
+def _hip(ot, name, *args):
+    rc = getattr(ot._lib, name)(*args)
+    assert rc == 0, (name, rc)
+
+
+class _Case:
+    """A fresh plan, inputs, and what ordinary launches write."""
+
+    def __init__(self, ot):
+        import torch
+        b = synthetic.apply_missing(synthetic.lattice_batch(9), 0.2, synthetic._rng(61))
+        self.plan = ot.Plan.from_batch(b)
+        self.M, self.X = synthetic.device_lattice_store(9, 61)
+        self.w = torch.randn((20, N), dtype=torch.float64, device="cuda",
+                             generator=torch.Generator("cuda").manual_seed(62))
+        self.ref = self.outputs()
+        self.run(self.ref, 1, None)
+        torch.cuda.synchronize()
+
+    @staticmethod
+    def outputs():
+        return {"L": _nan(20), "Ls": _nan(20), "Cs": _nan(24), "gM": _nan(20), "gX": _nan(3)}
+
+    def run(self, o, sched, stream):
+        self.plan.multipole_batched(self.M, self.X, o["L"], sched=sched, stream=stream)
+        self.plan.multipole_batched_save(self.M, self.X, o["Ls"], o["Cs"], sched=sched, stream=stream)
+        self.plan.multipole_backward_saved(self.M, self.X, self.w, o["Cs"], o["gM"], o["gX"], sched=sched, stream=stream)
+
+    def check(self, o, what):
+        import torch
+        for k, v in o.items():
+            assert torch.equal(v, self.ref[k]), (what, k)
+
+
+@pytest.mark.parametrize("sched", [0, 0x11, 0x31])
+def test_threads_on_the_per_thread_stream(ot, sched):
+    """Three threads launch one plan on hipStreamPerThread at the same time;
+    later launches on that handle are whole as well."""
+    import torch
+    c = _Case(ot)
+    outs = [[c.outputs() for _ in range(2)] for _ in range(3)]
+    torch.cuda.synchronize()
+    start = threading.Barrier(3)
+    errors = []
+
+    def work(mine):
+        try:
+            torch.cuda.set_device(0)
+            start.wait()
+            for o in mine:
+                c.run(o, sched, PER_THREAD)
+            _hip(ot, "hipStreamSynchronize", ctypes.c_void_p(PER_THREAD))
+        except Exception as e:  # noqa: BLE001 (reported below)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(m,)) for m in outs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for i, mine in enumerate(outs):
+        for o in mine:
+            c.check(o, "thread %d" % i)
+    o = c.outputs()
+    c.run(o, sched, PER_THREAD)
+    torch.cuda.synchronize()
+    c.check(o, "after the threads")
+
+
+@pytest.mark.parametrize("sched", [0, 0x11, 0x31])
+def test_two_executables_of_one_captured_graph(ot, sched):
+    """The forward recorded into one graph, instantiated twice, the two replayed
+    on two streams at the same time, with eager launches on a third."""
+    import torch
+    c = _Case(ot)
+    L, E = _nan(20), _nan(20)
+    s = [ctypes.c_void_p() for _ in range(3)]
+    for h in s:
+        _hip(ot, "hipStreamCreateWithFlags", ctypes.byref(h), 1)
+    graph, ex = ctypes.c_void_p(), [ctypes.c_void_p(), ctypes.c_void_p()]
+    torch.cuda.synchronize()
+    _hip(ot, "hipStreamBeginCapture", s[0], 1)
+    c.plan.multipole_batched(c.M, c.X, L, sched=sched, stream=s[0].value)
+    _hip(ot, "hipStreamEndCapture", s[0], ctypes.byref(graph))
+    for e in ex:
+        _hip(ot, "hipGraphInstantiate", ctypes.byref(e), graph, None, None, ctypes.c_size_t(0))
+    for rep in range(3):
+        L.fill_(float("nan"))
+        E.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for e, h in zip(ex, s):
+            _hip(ot, "hipGraphLaunch", e, h)
+        c.plan.multipole_batched(c.M, c.X, E, sched=sched, stream=s[2].value)
+        torch.cuda.synchronize()
+        assert torch.equal(L, c.ref["L"]) and torch.equal(E, c.ref["L"]), rep
+    # each executable alone, after they ran side by side
+    for e in ex:
+        L.fill_(float("nan"))
+        torch.cuda.synchronize()
+        _hip(ot, "hipGraphLaunch", e, s[0])
+        torch.cuda.synchronize()
+        assert torch.equal(L, c.ref["L"])
+    for e in ex:
+        _hip(ot, "hipGraphExecDestroy", e)
+    _hip(ot, "hipGraphDestroy", graph)
+    for h in s:
+        _hip(ot, "hipStreamDestroy", h)
+
+
+@pytest.mark.parametrize("sched", [0, 0x11, 0x31])
+def test_step_graph_replays_on_two_streams(ot, sched):
+    """The plan's step graph replayed on two streams without waiting between,
+    then once more after it was captured anew."""
+    import torch
+    c = _Case(ot)
+    o = c.outputs()
+    s = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for rep in range(2):
+        c.plan.step_graph_create_saved(c.M, c.X, o["Ls"], o["Cs"], c.w, o["gM"], o["gX"], sched, sched)
+        for times in (1, 4):
+            for v in o.values():
+                v.fill_(float("nan"))
+            torch.cuda.synchronize()
+            for k in range(times):
+                c.plan.step_graph_launch(s[k % 2])
+            torch.cuda.synchronize()
+            for k in ("Ls", "Cs", "gM", "gX"):
+                assert torch.equal(o[k], c.ref[k]), (rep, times, k)
