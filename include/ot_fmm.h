@@ -66,8 +66,8 @@ enum {
  * (OT_FMM_SCHED_BWD); the target-role pass accepts every schedule, the
  * source-role pass AUTO, W8 or W8P2. A byte left AUTO takes the plan's tuned
  * choice, else PERSISTENT | LOCAL from 640 targets (source role: store
- * sub-grids) on and no flags below; where AUTO finds no work counters left
- * (below) it drops PERSISTENT. */
+ * sub-grids) on and no flags below; where AUTO, tuned or not, finds no work
+ * counters left (below) it drops PERSISTENT. */
 enum {
     OT_FMM_SCHED_AUTO = 0,  /* the plan's tuned choice (ot_fmm_autotune), else as above */
     OT_FMM_SCHED_W8 = 1,

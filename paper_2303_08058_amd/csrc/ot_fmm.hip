@@ -224,7 +224,7 @@ constexpr int kTimedKernels = OT_FMM_NKERNELS;
 int pick(int sched, int tuned, int owners, int persistent_from)
 {
     if (sched != OT_FMM_SCHED_AUTO) return sched;
-    if (tuned) return tuned;
+    if (tuned) return tuned | kOptional;
     return owners >= persistent_from
                ? (OT_FMM_SCHED_W8 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL | kOptional)
                : OT_FMM_SCHED_W8;

@@ -164,3 +164,30 @@ def test_step_graph_replays_on_two_streams(ot, sched):
             torch.cuda.synchronize()
             for k in ("Ls", "Cs", "gM", "gX"):
                 assert torch.equal(o[k], c.ref[k]), (rep, times, k)
+
+
+def test_tuned_auto_on_more_streams_than_counters(ot):
+    """A tuned plan's AUTO launches on 70 streams are never refused, whatever
+    the tuner chose, and leave the explicit launches their 64 streams."""
+    import torch
+    c = _Case(ot)
+    o = c.outputs()
+    ex = ot.Executor(70, 0)
+    streams = [ex.stream(i) for i in range(70)]
+    # (the tuners' own launches name their schedules, on the last stream)
+    f, b = c.plan.autotune_saved(c.M, c.X, o["Ls"], o["Cs"], c.w, o["gM"], o["gX"], stream=streams[-1])
+    c.plan.autotune(c.M, c.X, o["L"], stream=streams[-1])
+    for i, s in enumerate(streams):
+        for v in o.values():
+            v.fill_(float("nan"))
+        torch.cuda.synchronize()
+        c.run(o, 0, s)
+        torch.cuda.synchronize()
+        c.check(o, ("stream", i, hex(f), hex(b)))
+    for s in streams[-64:]:
+        c.run(o, 0x11, s)
+        torch.cuda.synchronize()
+        c.check(o, "explicit")
+    with pytest.raises(ot.OtFmmError):
+        c.plan.multipole_batched(c.M, c.X, o["L"], sched=0x11, stream=streams[0])
+    ex.close()
