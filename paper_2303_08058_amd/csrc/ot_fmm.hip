@@ -155,7 +155,9 @@ constexpr int kWideRounds = 3;
 // round: eight wavefronts a plane take 114 us (205) for them, k_cells 7 (14) a
 // target. 150 targets forward 590 -> 528 us, 210 782 -> 720, 480 1544 -> 1488;
 // with saved sums 1195 -> 1035, 1594 -> 1431, 3173 -> 3039. The split depends on the
-// number of targets alone, so every schedule gives the same result.
+// number of targets alone, so every schedule gives the same result; both launches
+// go in index order (longest work first in the main one: 100 to 480 targets of
+// three boxes within 0.7% of it either way).
 constexpr int kCellRest = 12;
 
 // Every shape selects the same kernel; the tuners try the flags on this one.
@@ -216,6 +218,26 @@ constexpr int kOptional = 0x100;
 // ms, 567: 3.67 + 3.73 -> 3.60 + 3.69; 448, 512 and 576, whole rounds, unchanged).
 constexpr int kPersistentOwners = 640;
 constexpr int kPersistentOwnersSaved = 449;
+
+// How the targets (or store sub-grids) of a pass go over the chip: by k_cells,
+// by 8 wavefronts a plane, or by the work-groups of 4 wavefronts with `rest`
+// of them in a launch of their own.
+constexpr int kTargetParts = 4;  // work-groups of 4 wavefronts a target
+struct Split {
+    bool cells, wide;
+    int rest;
+    // the forms that work counters, and an order of the owners, make a difference to
+    bool counted() const { return !cells && !wide && rest == 0; }
+    bool ordered() const { return !cells && rest == 0; }
+};
+Split split_of(int owners, int n_cu)
+{
+    if (owners <= kCellOwners) return {true, false, 0};
+    if (owners * (int64_t)kSub <= (int64_t)kWideRounds * n_cu) return {false, true, 0};  // too few entries to deal out
+    const int round = n_cu / kTargetParts;
+    const int rest = round > 0 ? owners % round : 0;
+    return {false, false, owners >= kPersistentOwners || 2 * rest > round ? 0 : rest};
+}
 
 // kernels timed by the plan's events (ot_fmm_plan_kernel_times)
 constexpr int kTimedKernels = OT_FMM_NKERNELS;
@@ -385,23 +407,20 @@ int launch_parts(KParams kp, int owners, int* counter, int n_cu, hipStream_t str
 }
 
 template <int MODE>
-int launch_any(const KParams& kp, int owners, int* counter, int n_cu, hipStream_t stream)
+int launch_any(const KParams& kp, const Split& sp, int owners, int* counter, int n_cu, hipStream_t stream)
 {
-    if (owners <= kCellOwners) return launch_cells<MODE>(kp, owners, stream);
-    if (owners * (int64_t)kSub <= (int64_t)kWideRounds * n_cu)
-        return launch_parts<MODE, 1, 8>(kp, owners, nullptr, n_cu, stream);  // too few entries to deal out
+    if (sp.cells) return launch_cells<MODE>(kp, owners, stream);
+    if (sp.wide) return launch_parts<MODE, 1, 8>(kp, owners, nullptr, n_cu, stream);
     constexpr int kz = planes_per_wave<MODE>(), rs = 2 * kz;
-    const int round = n_cu / parts_per_target(kz, rs);
-    const int rest = round > 0 ? owners % round : 0;
-    if (owners >= kPersistentOwners || rest == 0 || 2 * rest > round)
-        return launch_parts<MODE, kz, rs>(kp, owners, counter, n_cu, stream);
+    static_assert(parts_per_target(kz, rs) == kTargetParts, "work-groups a target");
+    if (sp.rest == 0) return launch_parts<MODE, kz, rs>(kp, owners, counter, n_cu, stream);
     KParams part = kp;
     part.order = nullptr;
-    int rc = launch_parts<MODE, kz, rs>(part, owners - rest, nullptr, n_cu, stream);
+    int rc = launch_parts<MODE, kz, rs>(part, owners - sp.rest, nullptr, n_cu, stream);
     if (rc) return rc;
-    part.first = owners - rest;
-    return rest <= kCellRest ? launch_cells<MODE>(part, rest, stream)
-                             : launch_parts<MODE, 1, 8>(part, rest, nullptr, n_cu, stream);
+    part.first = owners - sp.rest;
+    return sp.rest <= kCellRest ? launch_cells<MODE>(part, sp.rest, stream)
+                                : launch_parts<MODE, 1, 8>(part, sp.rest, nullptr, n_cu, stream);
 }
 
 // The work order of a launch: XCD-aware (OT_FMM_SCHED_LOCAL) or longest work
@@ -426,16 +445,17 @@ int launch_timed(ot_fmm_plan plan, int which, KParams kp, int sched, hipStream_t
 {
     constexpr bool rev = ModeTraits<MODE>::source_role;
     const int owners = rev ? plan->S : plan->T;
+    const Split sp = split_of(owners, plan->n_cu);
     int* c = nullptr;
-    if (sched & OT_FMM_SCHED_PERSISTENT) {
+    if ((sched & OT_FMM_SCHED_PERSISTENT) && sp.counted()) {
         const int rs = counter_slot(plan, stream, (sched & kOptional) != 0, &c);
         if (rs) return rs;
     }
-    apply_order(kp, plan, sched, rev, c != nullptr);
+    if (sp.ordered()) apply_order(kp, plan, sched, rev, c != nullptr);
     std::pair<hipEvent_t, hipEvent_t> ev;
     int rc = timing_begin(plan, which, stream, &ev);
     if (rc) return rc;
-    if ((rc = launch_any<MODE>(kp, owners, c, plan->n_cu, stream))) return rc;
+    if ((rc = launch_any<MODE>(kp, sp, owners, c, plan->n_cu, stream))) return rc;
     return timing_end(ev, stream);
 }
 
@@ -673,6 +693,18 @@ void free_plan_memory(ot_fmm_plan p)
     p->d_cf_entries = nullptr;
     p->d_cf_cells = nullptr;
     p->d_cf_mask = nullptr;
+}
+
+// The flag combinations that differ for a pass over `owners`: what the tuners
+// time and keep.
+std::vector<int> distinct_flags(int owners, int n_cu)
+{
+    const Split sp = split_of(owners, n_cu);
+    std::vector<int> flags = {0};
+    if (sp.counted()) flags.push_back(OT_FMM_SCHED_PERSISTENT);
+    if (sp.ordered()) flags.push_back(OT_FMM_SCHED_LOCAL);
+    if (sp.counted()) flags.push_back(OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL);
+    return flags;
 }
 
 // Work order: longest work first (a greedy longest-processing-time list for
@@ -1543,11 +1575,10 @@ int ot_fmm_autotune_saved(ot_fmm_plan plan, const double* M, const double* com, 
         OT_HIP(hipEventElapsedTime(ms, ev.a, ev.b));
         return OT_FMM_OK;
     };
-    const int kFlags[4] = {0, OT_FMM_SCHED_PERSISTENT, OT_FMM_SCHED_LOCAL,
-                           OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL};
+    const std::vector<int> t_flags = distinct_flags(plan->T, plan->n_cu), s_flags = distinct_flags(plan->S, plan->n_cu);
     int best_f = kTunedShape, best_b = kTunedShape;
     float best_fms = 3.0e38f, best_bms = 3.0e38f;
-    for (int f : kFlags) {
+    for (int f : t_flags) {
         const int cand = kTunedShape | f;
         float ms = 0.0f;
         if (!rc) rc = time_it([&] { return fwd_save_batched(plan, M, com, L, Cs, cand, s); }, &ms);
@@ -1558,7 +1589,7 @@ int ot_fmm_autotune_saved(ot_fmm_plan plan, const double* M, const double* com, 
     }
     // the adjoint is timed on the sums of the last forward (any schedule's
     // sums are valid)
-    for (int f : kFlags) {
+    for (int f : s_flags) {
         const int cand = kTunedShape | f;
         float ms = 0.0f;
         if (!rc) rc = time_it([&] { return bwd_saved_batched(plan, M, com, gL, Cs, gM, gcom, cand, s); }, &ms);
@@ -1632,11 +1663,10 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
         OT_HIP(hipEventElapsedTime(ms, e0, e1));
         return OT_FMM_OK;
     };
-    // every combination of the persistent launch and the XCD-aware order, for
+    // the combinations of the persistent launch and the XCD-aware order, for
     // each pass on its own: the forward, then the source-role pass, then the
     // target-role pass
-    const int kFlags[4] = {0, OT_FMM_SCHED_PERSISTENT, OT_FMM_SCHED_LOCAL,
-                           OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL};
+    const std::vector<int> t_flags = distinct_flags(plan->T, plan->n_cu), s_flags = distinct_flags(plan->S, plan->n_cu);
     int best_f = kTunedShape;
     float best_ms = 3.0e38f;
     auto try_fwd = [&](int cand) -> int {
@@ -1648,7 +1678,7 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
         }
         return r;
     };
-    for (int f : kFlags)
+    for (int f : t_flags)
         if (!rc) rc = try_fwd(kTunedShape | f);
     int best_b = OT_FMM_SCHED_BWD(kTunedShape, kTunedShape);
     if (!rc && with_bwd) {
@@ -1665,10 +1695,10 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
             return r;
         };
         best_ms = 3.0e38f;
-        for (int f : kFlags)
+        for (int f : s_flags)
             if (!rc) rc = try_pass(1, kTunedShape | f, &best_s);
         best_ms = 3.0e38f;
-        for (int f : kFlags)
+        for (int f : t_flags)
             if (!rc) rc = try_pass(2, kTunedShape | f, &best_t);
         best_b = best_t | (best_s << 8);
         // the target-role trials accumulated into gcom: leave valid results
@@ -1931,7 +1961,7 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
         for (int k = 0; k <= nxcd; ++k) kp.piece_off[k] = (int)((int64_t)T * k / nxcd);
     }
     kp.invalid = head + 16;  // any: every element of L becomes NaN
-    return launch_any<MODE_FWD_STORE>(kp, T, head, ncu, s);
+    return launch_any<MODE_FWD_STORE>(kp, split_of(T, ncu), T, head, ncu, s);
 }
 
 int ot_fmm_noalloc_status(int32_t* invalid, int32_t* first_invalid)

@@ -166,6 +166,24 @@ def test_step_graph_replays_on_two_streams(ot, sched):
                 assert torch.equal(o[k], c.ref[k]), (rep, times, k)
 
 
+def _plan(ot, n, k=None, periodic=True):
+    """The first k sub-grids of a lattice of n^3, all of them targets."""
+    import numpy as np
+    import torch
+    k = k or n ** 3
+    full = synthetic.lattice_batch(n, periodic=periodic)
+    to = np.full(n ** 3 + 1, -1, np.int32)
+    to[:k] = np.arange(k)
+    b = {"S": k, "T": k, "tgt": np.arange(k, dtype=np.int32), "nbr": to[full["nbr"][:k]],
+         "shift": full["shift"][:k] if periodic else None, "period": full["period"]}
+    M, X = synthetic.device_lattice_store(n, 71)
+    M, X = M[:, :k * 512].contiguous(), X[:, :k * 512].contiguous()
+    out = {c: torch.full((r, k * 512), float("nan"), dtype=torch.float64, device="cuda")
+           for c, r in (("L", 20), ("Cs", 24), ("gM", 20), ("gX", 3))}
+    w = torch.ones((20, k * 512), dtype=torch.float64, device="cuda")
+    return ot.Plan.from_batch(b), M, X, w, out
+
+
 def test_tuned_auto_on_more_streams_than_counters(ot):
     """A tuned plan's AUTO launches on 70 streams are never refused, whatever
     the tuner chose, and leave the explicit launches their 64 streams."""
@@ -191,3 +209,33 @@ def test_tuned_auto_on_more_streams_than_counters(ot):
     with pytest.raises(ot.OtFmmError):
         c.plan.multipole_batched(c.M, c.X, o["L"], sched=0x11, stream=streams[0])
     ex.close()
+
+
+@pytest.mark.parametrize("n,k", [(2, 8), (3, 27), (6, 130), (6, 150)])
+def test_launches_without_counters_are_not_limited_by_them(ot, n, k):
+    """Few targets, 8 wavefronts a plane, a rest: an explicit persistent
+    schedule takes no counters there, so a 65th stream is as good as any."""
+    import torch
+    plan, M, X, w, o = _plan(ot, n, k, periodic=n > 2)
+    ref = torch.empty_like(o["L"])
+    plan.multipole_batched(M, X, ref, sched=1)
+    ex = ot.Executor(66, 0)
+    torch.cuda.synchronize()
+    for i in range(66):
+        o["L"].fill_(float("nan"))
+        torch.cuda.synchronize()
+        plan.multipole_batched(M, X, o["L"], sched=0x11, stream=ex.stream(i))
+        torch.cuda.synchronize()
+        assert torch.equal(o["L"], ref), i
+    ex.close()
+
+
+@pytest.mark.parametrize("n,k,flags", [(2, 8, {0}), (3, 27, {0, 0x20}), (6, 130, {0}),
+                                       (5, 120, {0, 0x10, 0x20, 0x30})])
+def test_tuners_choose_among_schedules_that_differ(ot, n, k, flags):
+    """Where a flag makes no difference the tuners do not keep it."""
+    plan, M, X, w, o = _plan(ot, n, k, periodic=n > 2)
+    f, b = plan.autotune(M, X, o["L"], w, o["gM"], o["gX"])
+    fs, bs = plan.autotune_saved(M, X, o["L"], o["Cs"], w, o["gM"], o["gX"])
+    for s in (f, b & 0xff, b >> 8, fs, bs):
+        assert s & 0xf in (1, 3) and s & 0x30 in flags, hex(s)
