@@ -69,7 +69,8 @@ enum {
  * sub-grids) on and no flags below; where AUTO, tuned or not, finds no work
  * counters left (below) it drops PERSISTENT.
  * The flags are accepted for every number of targets and make a difference to
- * some (on 256 CUs): LOCAL above 20, PERSISTENT above 96, and neither where
+ * some (on 256 CUs): LOCAL above 20 (12 to 20 if few of their neighbours are
+ * missing), PERSISTENT above 96, and neither where
  * the targets past whole rounds of 64 go in a launch of their own (97 to 639
  * targets that leave a rest of 1 to 32). A launch that takes no work counters
  * for one of these reasons is not limited by their number. */

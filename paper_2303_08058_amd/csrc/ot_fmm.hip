@@ -135,12 +135,31 @@ int launch_cells(const KParams& kp, int owners, hipStream_t stream)
     return OT_FMM_OK;
 }
 
-// Up to this many targets (or store sub-grids) k_cells takes no longer than the
-// work-groups of k_interact, whose time does not fall below that of one target:
-// forward of 18 targets of an open box 84 us against 112, with saved sums 168
-// against 198, of 27 with every neighbour 184 and 378 against 116 and 205 (k_cells'
-// time goes with the pairs, which the host does not know for tables on the device).
+// k_cells takes up to this many targets (or store sub-grids) of a chip of 256
+// CUs. Its time goes with the pairs, that of the other forms does not fall below
+// one target's: where every neighbour is there, k_cells is ahead up to 15 (forward,
+// 113 us against 117), in an open box up to 24 (117 against 116), with a third of
+// the neighbours missing up to 20 (113 against 117). The forward without a plan has
+// its table on the device, where the host cannot count pairs, and gives the plan's
+// result bit for bit, so the forward goes by the count alone: 20, at which it loses
+// 28% (151 against 118) to the other form with every neighbour and wins 18% in an
+// open box (95 against 116). The other passes are also held to the pairs of
+// cell_pairs() targets.
 constexpr int kCellOwners = 20;
+constexpr int kCus = 256;
+
+// A target's pairs with every neighbour there, and how many such targets' pairs
+// take k_cells as long as the 8 wavefronts a plane of up to 32 targets (256
+// CUs; k_cells against them with every neighbour, us): forward with saved sums 12
+// 186 / 202, 13 204 / 202; target role 12 401 / 412, 13 414 / 412 (with the source
+// role of 64); full truncation with saved sums 16 268 / 281, 17 283 / 282, target
+// role the same (587 / 596, 716 / 715); its forward 18 182 / 199, 20 200 / 199.
+constexpr int64_t kTargetPairs = (int64_t)kStencilHost.count[0] * kSub3;
+constexpr int cell_pairs(int sums)
+{
+    if (sums == SUMS_X3) return 19;
+    return sums == SUMS_X4 || sums == SUMS_X4T ? 16 : 12;
+}
 
 // Up to this many work-groups of 8 wavefronts a CU they are ahead of those of
 // 4: forward of 32 / 64 / 80 / 100 targets 114 / 241 / 356 / 474 us against (two
@@ -155,7 +174,7 @@ constexpr int kWideRounds = 3;
 // round: eight wavefronts a plane take 114 us (205) for them, k_cells 7 (14) a
 // target. 150 targets forward 590 -> 528 us, 210 782 -> 720, 480 1544 -> 1488;
 // with saved sums 1195 -> 1035, 1594 -> 1431, 3173 -> 3039. The split depends on the
-// number of targets alone, so every schedule gives the same result; both launches
+// plan alone, so every schedule gives the same result; both launches
 // go in index order (longest work first in the main one: 100 to 480 targets of
 // three boxes within 0.7% of it either way).
 constexpr int kCellRest = 12;
@@ -230,9 +249,14 @@ struct Split {
     bool counted() const { return !cells && !wide && rest == 0; }
     bool ordered() const { return !cells && rest == 0; }
 };
-Split split_of(int owners, int n_cu)
+// pairs: of the pass (0: not known, which only the forward's rule does not need)
+template <int MODE>
+Split split_of(int owners, int64_t pairs, int n_cu)
 {
-    if (owners <= kCellOwners) return {true, false, 0};
+    constexpr int sums = ModeTraits<MODE>::sums;
+    if ((int64_t)owners * kCus <= (int64_t)kCellOwners * n_cu &&
+        (sums == SUMS_F3 || pairs * kCus <= cell_pairs(sums) * kTargetPairs * n_cu))
+        return {true, false, 0};
     if (owners * (int64_t)kSub <= (int64_t)kWideRounds * n_cu) return {false, true, 0};  // too few entries to deal out
     const int round = n_cu / kTargetParts;
     const int rest = round > 0 ? owners % round : 0;
@@ -419,7 +443,7 @@ int launch_any(const KParams& kp, const Split& sp, int owners, int* counter, int
     int rc = launch_parts<MODE, kz, rs>(part, owners - sp.rest, nullptr, n_cu, stream);
     if (rc) return rc;
     part.first = owners - sp.rest;
-    return sp.rest <= kCellRest ? launch_cells<MODE>(part, sp.rest, stream)
+    return sp.rest * kCus <= kCellRest * n_cu ? launch_cells<MODE>(part, sp.rest, stream)
                                 : launch_parts<MODE, 1, 8>(part, sp.rest, nullptr, n_cu, stream);
 }
 
@@ -445,7 +469,7 @@ int launch_timed(ot_fmm_plan plan, int which, KParams kp, int sched, hipStream_t
 {
     constexpr bool rev = ModeTraits<MODE>::source_role;
     const int owners = rev ? plan->S : plan->T;
-    const Split sp = split_of(owners, plan->n_cu);
+    const Split sp = split_of<MODE>(owners, plan->pairs, plan->n_cu);
     int* c = nullptr;
     if ((sched & OT_FMM_SCHED_PERSISTENT) && sp.counted()) {
         const int rs = counter_slot(plan, stream, (sched & kOptional) != 0, &c);
@@ -695,11 +719,11 @@ void free_plan_memory(ot_fmm_plan p)
     p->d_cf_mask = nullptr;
 }
 
-// The flag combinations that differ for a pass over `owners`: what the tuners
-// time and keep.
-std::vector<int> distinct_flags(int owners, int n_cu)
+// The flag combinations that differ for a pass: what the tuners time and keep.
+template <int MODE>
+std::vector<int> distinct_flags(const ot_fmm_plan_s* plan)
 {
-    const Split sp = split_of(owners, n_cu);
+    const Split sp = split_of<MODE>(ModeTraits<MODE>::source_role ? plan->S : plan->T, plan->pairs, plan->n_cu);
     std::vector<int> flags = {0};
     if (sp.counted()) flags.push_back(OT_FMM_SCHED_PERSISTENT);
     if (sp.ordered()) flags.push_back(OT_FMM_SCHED_LOCAL);
@@ -1575,10 +1599,9 @@ int ot_fmm_autotune_saved(ot_fmm_plan plan, const double* M, const double* com, 
         OT_HIP(hipEventElapsedTime(ms, ev.a, ev.b));
         return OT_FMM_OK;
     };
-    const std::vector<int> t_flags = distinct_flags(plan->T, plan->n_cu), s_flags = distinct_flags(plan->S, plan->n_cu);
     int best_f = kTunedShape, best_b = kTunedShape;
     float best_fms = 3.0e38f, best_bms = 3.0e38f;
-    for (int f : t_flags) {
+    for (int f : distinct_flags<MODE_FS_STORE>(plan)) {
         const int cand = kTunedShape | f;
         float ms = 0.0f;
         if (!rc) rc = time_it([&] { return fwd_save_batched(plan, M, com, L, Cs, cand, s); }, &ms);
@@ -1589,7 +1612,7 @@ int ot_fmm_autotune_saved(ot_fmm_plan plan, const double* M, const double* com, 
     }
     // the adjoint is timed on the sums of the last forward (any schedule's
     // sums are valid)
-    for (int f : s_flags) {
+    for (int f : distinct_flags<MODE_B2S_STORE>(plan)) {
         const int cand = kTunedShape | f;
         float ms = 0.0f;
         if (!rc) rc = time_it([&] { return bwd_saved_batched(plan, M, com, gL, Cs, gM, gcom, cand, s); }, &ms);
@@ -1666,7 +1689,6 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
     // the combinations of the persistent launch and the XCD-aware order, for
     // each pass on its own: the forward, then the source-role pass, then the
     // target-role pass
-    const std::vector<int> t_flags = distinct_flags(plan->T, plan->n_cu), s_flags = distinct_flags(plan->S, plan->n_cu);
     int best_f = kTunedShape;
     float best_ms = 3.0e38f;
     auto try_fwd = [&](int cand) -> int {
@@ -1678,7 +1700,7 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
         }
         return r;
     };
-    for (int f : t_flags)
+    for (int f : distinct_flags<MODE_FWD_STORE>(plan))
         if (!rc) rc = try_fwd(kTunedShape | f);
     int best_b = OT_FMM_SCHED_BWD(kTunedShape, kTunedShape);
     if (!rc && with_bwd) {
@@ -1695,10 +1717,10 @@ int ot_fmm_autotune(ot_fmm_plan plan, const double* M, const double* com, double
             return r;
         };
         best_ms = 3.0e38f;
-        for (int f : s_flags)
+        for (int f : distinct_flags<MODE_B2_STORE>(plan))
             if (!rc) rc = try_pass(1, kTunedShape | f, &best_s);
         best_ms = 3.0e38f;
-        for (int f : t_flags)
+        for (int f : distinct_flags<MODE_B1_STORE>(plan))
             if (!rc) rc = try_pass(2, kTunedShape | f, &best_t);
         best_b = best_t | (best_s << 8);
         // the target-role trials accumulated into gcom: leave valid results
@@ -1961,7 +1983,7 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
         for (int k = 0; k <= nxcd; ++k) kp.piece_off[k] = (int)((int64_t)T * k / nxcd);
     }
     kp.invalid = head + 16;  // any: every element of L becomes NaN
-    return launch_any<MODE_FWD_STORE>(kp, split_of(T, ncu), T, head, ncu, s);
+    return launch_any<MODE_FWD_STORE>(kp, split_of<MODE_FWD_STORE>(T, 0, ncu), T, head, ncu, s);
 }
 
 int ot_fmm_noalloc_status(int32_t* invalid, int32_t* first_invalid)
