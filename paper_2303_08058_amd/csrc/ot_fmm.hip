@@ -228,20 +228,29 @@ constexpr int kCounterSlots = 2 * kEagerSlots + kGraphSlots;
 // A schedule that AUTO stands for may be given up for an ordinary launch.
 constexpr int kOptional = 0x100;
 
+// Work-groups of 4 wavefronts a target; a round of the chip is one on every CU.
+constexpr int kTargetParts = 4;
+constexpr int round_of(int n_cu) { return n_cu / kTargetParts; }
+
 // AUTO of an untuned plan: persistent in the XCD-aware pieces from this many
-// targets (or store sub-grids) on, an ordinary launch, longest work first,
-// below. The pieces cut the staging traffic (forward of 16384 sub-grids 57.8
-// -> 52.6 ms, 4096: 14.2 -> 13.4); with few work-groups a CU they end less
-// evenly (forward of 576: 1.85 -> 1.91 ms, both adjoint passes 6.93 -> 7.28). The
-// two launches of the saved sums gain from 449 on (486: 3.26 + 3.31 -> 3.19 + 3.24
-// ms, 567: 3.67 + 3.73 -> 3.60 + 3.69; 448, 512 and 576, whole rounds, unchanged).
-constexpr int kPersistentOwners = 640;
-constexpr int kPersistentOwnersSaved = 449;
+// rounds (10 of 64 targets or store sub-grids on 256 CUs) on, an ordinary
+// launch, longest work first, below. The pieces cut the staging traffic (forward
+// of 16384 sub-grids 57.8 -> 52.6 ms, 4096: 14.2 -> 13.4); with few work-groups a
+// CU they end less evenly (forward of 576: 1.83 -> 1.92 ms, both adjoint passes
+// 7.45 -> 7.58; forward with saved sums and one-pass adjoint of 486 / 512 / 567 /
+// 610 / 630 targets of three boxes -1 to -2% / -1 to 1% / 0 to 2% / -1 to 1% / -1 to
+// 2%). Only the two launches of the full truncation, with half as much again to
+// do for what is staged, gain from past 7 rounds on: -1 to -3% / -1 to -2% / -3 to
+// -4% / -3 to -5% / -1 to -2% at the same counts.
+constexpr int kPersistentRounds = 10;
+bool persistent_from(int owners, int n_cu, bool full_saved = false)
+{
+    return full_saved ? owners > 7 * round_of(n_cu) : owners >= kPersistentRounds * round_of(n_cu);
+}
 
 // How the targets (or store sub-grids) of a pass go over the chip: by k_cells,
 // by 8 wavefronts a plane, or by the work-groups of 4 wavefronts with `rest`
 // of them in a launch of their own.
-constexpr int kTargetParts = 4;  // work-groups of 4 wavefronts a target
 struct Split {
     bool cells, wide;
     int rest;
@@ -258,22 +267,20 @@ Split split_of(int owners, int64_t pairs, int n_cu)
         (sums == SUMS_F3 || pairs * kCus <= cell_pairs(sums) * kTargetPairs * n_cu))
         return {true, false, 0};
     if (owners * (int64_t)kSub <= (int64_t)kWideRounds * n_cu) return {false, true, 0};  // too few entries to deal out
-    const int round = n_cu / kTargetParts;
+    const int round = round_of(n_cu);
     const int rest = round > 0 ? owners % round : 0;
-    return {false, false, owners >= kPersistentOwners || 2 * rest > round ? 0 : rest};
+    return {false, false, persistent_from(owners, n_cu) || 2 * rest > round ? 0 : rest};
 }
 
 // kernels timed by the plan's events (ot_fmm_plan_kernel_times)
 constexpr int kTimedKernels = OT_FMM_NKERNELS;
 
-// The schedule of one pass over `owners` targets or store sub-grids.
-int pick(int sched, int tuned, int owners, int persistent_from)
+// The schedule of one pass; persistent: what AUTO of an untuned plan is.
+int pick(int sched, int tuned, bool persistent)
 {
     if (sched != OT_FMM_SCHED_AUTO) return sched;
     if (tuned) return tuned | kOptional;
-    return owners >= persistent_from
-               ? (OT_FMM_SCHED_W8 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL | kOptional)
-               : OT_FMM_SCHED_W8;
+    return persistent ? (OT_FMM_SCHED_W8 | OT_FMM_SCHED_PERSISTENT | OT_FMM_SCHED_LOCAL | kOptional) : OT_FMM_SCHED_W8;
 }
 
 }  // namespace
@@ -498,7 +505,7 @@ int fwd_batched(ot_fmm_plan plan, const double* M, const double* com, double* L,
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, plan->T, kPersistentOwners), stream);
+    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, persistent_from(plan->T, plan->n_cu)), stream);
 }
 
 // Forward with the full truncation: the same plan, tables and schedules as
@@ -518,7 +525,7 @@ int fwd_full_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_FULL_STORE>(plan, -1, kp, pick(sched, 0, plan->T, kPersistentOwners), stream);
+    return launch_timed<MODE_FULL_STORE>(plan, -1, kp, pick(sched, 0, persistent_from(plan->T, plan->n_cu)), stream);
 }
 
 // Adjoint of the batched forward (FULL: of the full truncation, with
@@ -537,8 +544,8 @@ int bwd_any(ot_fmm_plan plan, const double* M, const double* com, const double* 
     int tsched = sched & 0xff, ssched = (sched >> 8) & 0xff;
     if (FULL && (tsched & kShapeMask) == OT_FMM_SCHED_W16)
         return fail(OT_FMM_EINVAL, "16 wavefronts are not available for the full truncation's adjoint");
-    tsched = pick(tsched, FULL ? 0 : plan->tuned_bwd & 0xff, plan->T, kPersistentOwners);
-    ssched = pick(ssched, FULL ? 0 : plan->tuned_bwd >> 8, plan->S, kPersistentOwners);
+    tsched = pick(tsched, FULL ? 0 : plan->tuned_bwd & 0xff, persistent_from(plan->T, plan->n_cu));
+    ssched = pick(ssched, FULL ? 0 : plan->tuned_bwd >> 8, persistent_from(plan->S, plan->n_cu));
     const long NS = (long)plan->S * kSub3, NT = (long)plan->T * kSub3;
     // source role: owners are store sub-grids, sources the target cells that see them
     KParams b2{};
@@ -616,7 +623,7 @@ int fwd_save_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
     return launch_timed<kMode>(plan, FULL ? -1 : 3, kp,
-                               pick(sched, FULL ? 0 : plan->tuned_save, plan->T, kPersistentOwnersSaved), stream);
+                               pick(sched, FULL ? 0 : plan->tuned_save, persistent_from(plan->T, plan->n_cu, FULL)), stream);
 }
 
 // Forward with the angular-momentum correction of the force: L, and
@@ -640,8 +647,8 @@ int fwd_amc_batched(ot_fmm_plan plan, const double* M, const double* com, double
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_AMC_STORE>(plan, 5, kp, pick(sched, plan->tuned_save, plan->T, kPersistentOwnersSaved),
-                                        stream);
+    return launch_timed<MODE_AMC_STORE>(plan, 5, kp,
+                                        pick(sched, plan->tuned_save, persistent_from(plan->T, plan->n_cu)), stream);
 }
 
 // One-pass adjoint from the saved sums: the source-role pass over every store
@@ -673,7 +680,8 @@ int bwd_saved_batched(ot_fmm_plan plan, const double* M, const double* com, cons
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
     return launch_timed<kMode>(plan, FULL ? -1 : 4, kp,
-                               pick(sched, FULL ? 0 : plan->tuned_saved_bwd, plan->S, kPersistentOwnersSaved), stream);
+                               pick(sched, FULL ? 0 : plan->tuned_saved_bwd, persistent_from(plan->S, plan->n_cu, FULL)),
+                               stream);
 }
 
 int check_plan(ot_fmm_plan plan)
@@ -1978,7 +1986,7 @@ int ot_fmm_multipole_batched_noalloc(int32_t S, int32_t T, const int32_t* tgt, c
     kp.out_stride = NT;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = per[k];
-    if (T >= kPersistentOwners && nxcd <= kMaxPieces) {
+    if (persistent_from(T, ncu) && nxcd <= kMaxPieces) {
         kp.npieces = nxcd;
         for (int k = 0; k <= nxcd; ++k) kp.piece_off[k] = (int)((int64_t)T * k / nxcd);
     }
