@@ -166,6 +166,84 @@ def test_step_graph_replays_on_two_streams(ot, sched):
                 assert torch.equal(o[k], c.ref[k]), (rep, times, k)
 
 
+@pytest.mark.parametrize("sched", [0, 0x11, 0x31])
+def test_two_streams_in_flight(ot, sched):
+    """Every pass of one plan on two streams at once, twice on each."""
+    import torch
+    c = _Case(ot)
+    outs = [c.outputs() for _ in range(4)]
+    s = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        c.run(o, sched, s[i % 2])
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        c.check(o, "launch %d" % i)
+
+
+@pytest.mark.parametrize("sched", [0x11, 0x31])
+def test_three_launch_step_graph_beside_eager_launches(ot, sched):
+    """The three-launch step in the plan's graph, replayed while eager launches
+    of the same plan run on another stream; each replay against eager results."""
+    import torch
+    c = _Case(ot)
+    L, gM, gX, R = _nan(20), _nan(20), _nan(3), _nan(3)
+    c.plan.multipole_backward(c.M, c.X, c.w, gM, R, sched=0x0101)
+    c.plan.step_graph_create(c.M, c.X, L, c.w, gM, gX, sched, sched | sched << 8)
+    s = [torch.cuda.Stream(), torch.cuda.Stream()]
+    o = c.outputs()
+    for rep in range(3):
+        for t in (L, gM, gX, *o.values()):
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        c.plan.step_graph_launch(s[0])
+        c.run(o, sched, s[1])
+        torch.cuda.synchronize()
+        assert torch.equal(L, c.ref["L"]) and torch.equal(gM, c.ref["gM"]) and torch.equal(gX, R), rep
+        c.check(o, ("eager", rep))
+
+
+@pytest.mark.parametrize("sched", [0, 0x11, 0x31])
+def test_full_truncation_in_a_callers_graph(ot, sched):
+    """The full truncation's passes recorded into a caller's graph, replayed
+    three times beside eager ones (729 and 512 targets: AUTO is persistent for
+    its saved sums at both, for its forward at 729)."""
+    import torch
+    for n in (9, 8):
+        b = synthetic.apply_missing(synthetic.lattice_batch(n), 0.2, synthetic._rng(63))
+        plan = ot.Plan.from_batch(b)
+        M, X = synthetic.device_lattice_store(n, 63)
+        w = torch.ones((20, n ** 3 * 512), dtype=torch.float64, device="cuda")
+        nan = lambda: [torch.full((k, n ** 3 * 512), float("nan"), dtype=torch.float64, device="cuda")  # noqa: E731
+                       for k in (20, 20, 24, 20, 3, 20, 3)]
+
+        def run(o, sc, stream):
+            plan.multipole_batched_full(M, X, o[0], sched=sc, stream=stream)
+            plan.multipole_batched_save(M, X, o[1], o[2], sched=sc, stream=stream, full=True)
+            plan.multipole_backward_saved(M, X, w, o[2], o[3], o[4], sched=sc, stream=stream, full=True)
+            plan.multipole_backward_full(M, X, w, o[5], o[6], sched=sc | sc << 8, stream=stream)
+
+        ref, o, e = nan(), nan(), nan()
+        run(ref, 1, None)
+        s = [torch.cuda.Stream(), torch.cuda.Stream()]
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s[0]):
+            run(o, sched, s[0])
+        for rep in range(3):
+            for t in o + e:
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s[0]):
+                g.replay()
+            run(e, sched, s[1])
+            torch.cuda.synchronize()
+            for a, x, r in zip(o, e, ref):
+                assert torch.equal(a, r) and torch.equal(x, r), (n, rep)
+            junk = torch.randn(1 << 20, device="cuda").sum()  # eager work between replays
+            del junk
+
+
 def _plan(ot, n, k=None, periodic=True):
     """The first k sub-grids of a lattice of n^3, all of them targets."""
     import numpy as np

@@ -1,5 +1,6 @@
 """The rules that choose how a batched pass is split over the chip, at the
-counts where they change: few targets by their pairs, for each pass. Oracle and
+counts where they change: few targets by their pairs, and both sides of a rest
+that goes in a launch of its own, for each pass. Oracle and
 criterion as in test_gpu_parity.py (1e-12 per sub-grid and output order)."""
 import os
 import sys
@@ -112,3 +113,47 @@ def test_the_forward_without_a_plan_keeps_to_the_plans_split(ot, field):
             d = {q: torch.from_numpy(np.ascontiguousarray(batch[q])).cuda() for q in ("tgt", "nbr", "shift")}
             ot.ot_fmm_multipole_batched_noalloc(64, k, d["tgt"], d["nbr"], d["shift"], batch["period"], Md, Xd, R)
             assert np.array_equal(_host(L), _host(R)), (k, frac)
+
+
+@pytest.mark.parametrize("k", [21, 96, 97, 130, 150, 216])
+def test_both_sides_of_a_rest(ot, k):
+    """k of a periodic 6^3 lattice's sub-grids: the first and the last target of
+    whole rounds (64 targets) and of what is past them, every pass."""
+    rng = synthetic._rng(810 + k)
+    M, X = synthetic.store_field(6, rng, 2.0, 3.0, 0.6, sep=6.0)
+    full = synthetic.lattice_batch(6)
+    ids = np.sort(rng.permutation(216)[:k])
+    to = np.full(217, -1, np.int32)
+    to[ids] = np.arange(k)
+    cols = (ids[:, None] * SUB3 + np.arange(SUB3)).reshape(-1)
+    M, X = np.ascontiguousarray(M[:, cols]), np.ascontiguousarray(X[:, cols])
+    batch = {"S": k, "T": k, "tgt": np.arange(k, dtype=np.int32), "nbr": to[full["nbr"][ids]],
+             "shift": full["shift"][ids], "period": full["period"]}
+    w = synthetic.weights(k, 811)
+    plan = ot.Plan.from_batch(batch)
+    Md, Xd, wd = _dev(M), _dev(X), _dev(w)
+    main = k - k % 64
+    sel = np.unique(np.array([0, max(main - 1, 0), main % k, k - 1], np.int32))
+    n = k * SUB3
+    for fl in (False, True):
+        ref, A = oracle.batched_forward(batch, M, X, tsel=sel, want_abs=True, full=fl)
+        L, Ls, Cs = _nan(20, n), _nan(20, n), _nan(24, n)
+        (plan.multipole_batched_full if fl else plan.multipole_batched)(Md, Xd, L)
+        assert_parity(_pick(L, k, sel), ref, TOL, what="L", A=A)
+        plan.multipole_batched_save(Md, Xd, Ls, Cs, full=fl)
+        assert_parity(_pick(Ls, k, sel), ref, TOL, what="saved L", A=A)
+        check_saved(_pick(Cs, k, sel), batch, M, X, "Cs", tsel=sel, full=fl)
+        gM_ref, gX_ref = oracle.batched_backward(batch, M, X, w, ssel=sel, full=fl)
+        gM, gX, gM2, gX2 = _nan(20, n), _nan(3, n), _nan(20, n), _nan(3, n)
+        plan.multipole_backward_saved(Md, Xd, wd, Cs, gM, gX, full=fl)
+        (plan.multipole_backward_full if fl else plan.multipole_backward)(Md, Xd, wd, gM2, gX2)
+        assert np.array_equal(_host(gM), _host(gM2))
+        assert_parity(_pick(gM, k, sel), gM_ref, TOL, what="gM")
+        assert_parity(_pick(gX, k, sel), gX_ref, TOL, what="gX")
+        assert_parity(_pick(gX2, k, sel), gX_ref, TOL, what="three-launch gX")
+        if not fl:
+            dref, dA = oracle.batched_forward_amc(batch, M, X, tsel=sel, want_abs=True)
+            Lc, dF = _nan(20, n), _nan(3, n)
+            plan.multipole_batched_amc(Md, Xd, Lc, dF)
+            assert np.array_equal(_host(Lc), _host(Ls))
+            assert_parity(_pick(dF, k, sel), dref, TOL, what="dF", A=dA)
