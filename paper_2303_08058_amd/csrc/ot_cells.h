@@ -124,8 +124,8 @@ __device__ __forceinline__ int lanes_sum(double* v, int lane, int base, int coun
 // (4 of NT = 512) straight from memory (a source serves both cells of a pair),
 // and the partial sums meet by lane exchange and once through LDS. Work-groups
 // go to the XCDs in turn: each takes one z-plane of cells of every target, so
-// that an L2 holds the 11 to 19 source planes in reach instead of all (64
-// blocks on 16 streams 771 -> 726 us, with the exchange through registers). One
+// that an L2 holds the 18 source planes in reach instead of all 24 (64 blocks
+// as futures on 16 streams 737 us, 800 with the cells dealt in turn). One
 // sub-grid, forward: 8 us (145 with k_interact); with saved sums 11 (156); of
 // 18, 4.7 and 9.3 each. What bounds it then is the L1 (rows of up to 18 cells
 // of 23 components, read once a work-group) and the list and the merge, about

@@ -113,10 +113,10 @@ int launch(const KParams& kp, int nblocks, hipStream_t stream)
 }
 
 // The target cells of `owners` owners by k_cells: 512 threads for the pairs of
-// cells of a single sub-grid (256 work-groups), 256 for its multipole block
-// (a block takes as long with either, 13.6 us, but work-groups of 256 let
-// blocks on several streams share the CUs: 64 on 16 streams 730 us with 512,
-// 610 with 256, 680 with 128), else 128, whose sums are merged least often (8
+// cells of a single sub-grid (256 work-groups), 256 for its multipole block (one
+// block takes 12.7 us with them, 12.2 with 512, 15.9 with 128, but they let
+// blocks on several streams share the CUs: 64 as futures on 16 streams 737 us,
+// 908 with 512, 807 with 128), else 128, whose sums are merged least often (8
 // sub-grids forward 42 us with 256, 40 with 128, 42 with 64; with saved sums
 // 79, 71 and 79).
 template <int MODE>
@@ -171,7 +171,7 @@ constexpr int kWideRounds = 3;
 // its end, time goes in steps of a round (a work-group of 4 wavefronts a CU: 64
 // targets of 256 CUs, 209 us forward, 425 with saved sums). The targets past
 // the last whole round go in a launch of their own if they are at most half a
-// round: eight wavefronts a plane take 114 us (205) for them, k_cells 7 (14) a
+// round: eight wavefronts a plane take 117 us (202) for them, k_cells 7.4 (15.5) a
 // target. 150 targets forward 590 -> 528 us, 210 782 -> 720, 480 1544 -> 1488;
 // with saved sums 1195 -> 1035, 1594 -> 1431, 3173 -> 3039. The split depends on the
 // plan alone, so every schedule gives the same result; both launches

@@ -438,9 +438,12 @@ __device__ __forceinline__ void store_sums(const KParams& p, int owner, int cell
 // 16 bytes) a cell, odd rows at odd units. A 16-byte read serves 16 lanes per
 // cycle, two rows of the mirrored lane pattern: one of even, one of odd y,
 // each with 8 cells that differ modulo 8. The even row's units are even and
-// cover the even bank groups once, the odd row's the odd ones: no conflicts
-// (with records 22 doubles apart and rows packed freely, half of the LDS
-// cycles were conflicts). 70 KiB, so two work-groups fit a CU.
+// cover the even bank groups once, the odd row's the odd ones. Conflicts stay
+// all the same: 3.9 cycles an LDS instruction (10.4e9 on 2.67e9 in the forward
+// of 32768 sub-grids, 19.6e9 on 4.97e9 with saved sums), where records 22
+// doubles apart in freely packed rows had half of the LDS cycles. They do not
+// bound the kernel: a copy of it without LDS reads took 1% fewer clocks. 70
+// KiB, so two work-groups fit a CU.
 constexpr int kPlaneCells = 448;
 constexpr int kRecUnits = 10;                             // 16-byte reads of a record
 constexpr int kPlaneUnits = kPlaneCells * kRecUnits + kHalo;

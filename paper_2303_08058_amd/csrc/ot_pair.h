@@ -134,7 +134,6 @@ __device__ __forceinline__ void stage_record(const double* raw, double* rec)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-#ifndef OT_PAIR_HOST_RSQ
 __device__ __forceinline__ double rsqrt_fp64(double a)
 {
     // hardware estimate, then y (1 + e/2 + 3e^2/8) with e = 1 - a y^2
@@ -143,7 +142,6 @@ __device__ __forceinline__ double rsqrt_fp64(double a)
     y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
     return y;
 }
-#endif
 
 // Sum of the order-3 outputs c H_ijk(r), H the trace-free part of r r r
 // (kept: xxx, xxy, xxz, xyy, xyz, yyy, yyz), from cr = c r.
