@@ -66,14 +66,16 @@ enum {
  * (OT_FMM_SCHED_BWD); the target-role pass accepts every schedule, the
  * source-role pass AUTO, W8 or W8P2. A byte left AUTO takes the plan's tuned
  * choice, else (on 256 CUs) PERSISTENT | LOCAL from 640 targets (source role:
- * store sub-grids) on, the full truncation's saved-sums step from 449, and no
- * flags below; where AUTO, tuned or not, finds no work
- * counters left (below) it drops PERSISTENT.
+ * store sub-grids) on -- the corrected forward and the step with saved sums
+ * also from 449 to 512, the full truncation's from 449 -- and no flags below;
+ * where AUTO, tuned or not, finds no work counters left (below) it drops
+ * PERSISTENT.
  * The flags are accepted for every number of targets and make a difference to
  * some: LOCAL above 20 (12 to 20 if few of their neighbours are missing),
  * PERSISTENT above 96, and neither where the targets past whole rounds of 64
- * go in a launch of their own (97 to 639 targets, a rest of 1 to 32). A launch that takes no work counters
- * for one of these reasons is not limited by their number. */
+ * go in a launch of their own (97 to 639 targets, a rest of 1 to 32). A launch
+ * that takes no work counters for one of these reasons is not limited by their
+ * number. */
 enum {
     OT_FMM_SCHED_AUTO = 0,  /* the plan's tuned choice (ot_fmm_autotune), else as above */
     OT_FMM_SCHED_W8 = 1,

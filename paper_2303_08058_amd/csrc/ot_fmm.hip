@@ -236,16 +236,21 @@ constexpr int round_of(int n_cu) { return n_cu / kTargetParts; }
 // rounds (10 of 64 targets or store sub-grids on 256 CUs) on, an ordinary
 // launch, longest work first, below. The pieces cut the staging traffic (forward
 // of 16384 sub-grids 57.8 -> 52.6 ms, 4096: 14.2 -> 13.4); with few work-groups a
-// CU they end less evenly (forward of 576: 1.83 -> 1.92 ms, both adjoint passes
-// 7.45 -> 7.58; forward with saved sums and one-pass adjoint of 486 / 512 / 567 /
-// 610 / 630 targets of three boxes -1 to -2% / -1 to 1% / 0 to 2% / -1 to 1% / -1 to
-// 2%). Only the two launches of the full truncation, with half as much again to
-// do for what is staged, gain from past 7 rounds on: -1 to -3% / -1 to -2% / -3 to
-// -4% / -3 to -5% / -1 to -2% at the same counts.
+// CU they end less evenly (forward of 486 to 576 targets up to 6% slower). The
+// step with saved sums and the corrected forward do twice as much for what is
+// staged and gain in the eighth round already (449 to 512), the full truncation's
+// step, with three times as much, from there on. Both launches of a step, by the
+// persistent launch, on five boxes:
+//   targets           486       500       512       550       576       610       630
+//   total order    -3 to 0   -4 to -1  -3 to +1   0 to +2  +4 to +5  +1 to +4  +2 to +6 %
+//   full           -3 to 0   -2 to -1  -1 to  0  -5 to -3  -2 to -1  -3 to -2  -1 to +1 %
 constexpr int kPersistentRounds = 10;
-bool persistent_from(int owners, int n_cu, bool full_saved = false)
+enum Keeps { kPlain, kSaved, kSavedFull };
+bool persistent_from(int owners, int n_cu, Keeps keeps = kPlain)
 {
-    return full_saved ? owners > 7 * round_of(n_cu) : owners >= kPersistentRounds * round_of(n_cu);
+    const int round = round_of(n_cu);
+    if (owners >= kPersistentRounds * round) return true;
+    return keeps != kPlain && owners > 7 * round && (keeps == kSavedFull || owners <= 8 * round);
 }
 
 // How the targets (or store sub-grids) of a pass go over the chip: by k_cells,
@@ -505,7 +510,8 @@ int fwd_batched(ot_fmm_plan plan, const double* M, const double* com, double* L,
     kp.out_stride = (long)plan->T * kSub3;
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
-    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, persistent_from(plan->T, plan->n_cu)), stream);
+    return launch_timed<MODE_FWD_STORE>(plan, 0, kp, pick(sched, plan->tuned_fwd, persistent_from(plan->T, plan->n_cu)),
+                                        stream);
 }
 
 // Forward with the full truncation: the same plan, tables and schedules as
@@ -623,7 +629,9 @@ int fwd_save_batched(ot_fmm_plan plan, const double* M, const double* com, doubl
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
     return launch_timed<kMode>(plan, FULL ? -1 : 3, kp,
-                               pick(sched, FULL ? 0 : plan->tuned_save, persistent_from(plan->T, plan->n_cu, FULL)), stream);
+                               pick(sched, FULL ? 0 : plan->tuned_save,
+                                    persistent_from(plan->T, plan->n_cu, FULL ? kSavedFull : kSaved)),
+                               stream);
 }
 
 // Forward with the angular-momentum correction of the force: L, and
@@ -648,7 +656,8 @@ int fwd_amc_batched(ot_fmm_plan plan, const double* M, const double* com, double
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
     return launch_timed<MODE_AMC_STORE>(plan, 5, kp,
-                                        pick(sched, plan->tuned_save, persistent_from(plan->T, plan->n_cu)), stream);
+                                        pick(sched, plan->tuned_save, persistent_from(plan->T, plan->n_cu, kSaved)),
+                                        stream);
 }
 
 // One-pass adjoint from the saved sums: the source-role pass over every store
@@ -680,7 +689,8 @@ int bwd_saved_batched(ot_fmm_plan plan, const double* M, const double* com, cons
     kp.out_blk = nullptr;
     for (int k = 0; k < 3; ++k) kp.period[k] = plan->period[k];
     return launch_timed<kMode>(plan, FULL ? -1 : 4, kp,
-                               pick(sched, FULL ? 0 : plan->tuned_saved_bwd, persistent_from(plan->S, plan->n_cu, FULL)),
+                               pick(sched, FULL ? 0 : plan->tuned_saved_bwd,
+                                    persistent_from(plan->S, plan->n_cu, FULL ? kSavedFull : kSaved)),
                                stream);
 }
 
