@@ -456,7 +456,7 @@ int launch_any(const KParams& kp, const Split& sp, int owners, int* counter, int
     if (rc) return rc;
     part.first = owners - sp.rest;
     return sp.rest * kCus <= kCellRest * n_cu ? launch_cells<MODE>(part, sp.rest, stream)
-                                : launch_parts<MODE, 1, 8>(part, sp.rest, nullptr, n_cu, stream);
+                                              : launch_parts<MODE, 1, 8>(part, sp.rest, nullptr, n_cu, stream);
 }
 
 // The work order of a launch: XCD-aware (OT_FMM_SCHED_LOCAL) or longest work
